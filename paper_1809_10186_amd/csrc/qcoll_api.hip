@@ -233,7 +233,7 @@ qcoll_status qcoll_eval(qcoll_plan plan, int64_t batch, const double *f, double 
   const long n3 = plan->p.n3();
   if ((const void *)f < (const void *)(Q + batch * n3) && (const void *)Q < (const void *)(f + batch * n3))
     return fail(QCOLL_EINVAL, "Q must not overlap f");
-  const qcoll::Layout lay = qcoll::make_layout(plan->p, batch, 0);
+  const qcoll::Layout lay = qcoll::make_layout(plan->p, batch, 0, 0, ws_bytes);
   if (!ws || ws_bytes < lay.total) return fail(QCOLL_EWORKSPACE, "workspace missing or smaller than qcoll_workspace_bytes");
   qcoll_status st = check_device(plan->p);
   if (st != QCOLL_OK) return st;
@@ -324,18 +324,19 @@ qcoll_status qcoll_dg_collide(qcoll_plan plan, int64_t n_elem, int32_t K, int32_
   const size_t n3 = size_t(plan->p.n3());
   const size_t terms = size_t(n_elem) * R;
   if (terms > size_t(0x7fffffff)) return fail(QCOLL_EINVAL, "n_elem * R too large");
-  const size_t need = qcoll_dg_workspace_bytes(plan, n_elem, K, R);
-  if (!ws || ws_bytes < need) return fail(QCOLL_EWORKSPACE, "workspace missing or smaller than qcoll_dg_workspace_bytes");
+  auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
+  const size_t vols = 2 * al(terms * n3 * sizeof(double));
+  const qcoll::Layout lay = qcoll::make_layout(plan->p, int64_t(terms), 0, 0, ws_bytes > vols ? ws_bytes - vols : 0);
+  if (!ws || ws_bytes < vols + lay.total)
+    return fail(QCOLL_EWORKSPACE, "workspace missing or smaller than qcoll_dg_workspace_bytes");
   qcoll_status st = check_device(plan->p);
   if (st != QCOLL_OK) return st;
-  auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
   char *w = static_cast<char *>(ws);
   double *Hd = reinterpret_cast<double *>(w);
   double *Qd = reinterpret_cast<double *>(w + al(terms * n3 * sizeof(double)));
   void *ews = w + 2 * al(terms * n3 * sizeof(double));
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = qcoll::launch_dg_contract(T, F, Hd, n_elem, R, K, long(n3), s)) != QCOLL_OK) return st;
-  const qcoll::Layout lay = qcoll::make_layout(plan->p, int64_t(terms), 0);
   if ((st = qcoll::launch_eval(plan->p, int64_t(terms), Hd, Qd, ews, lay, s)) != QCOLL_OK) return st;
   if (conserve && (st = qcoll::launch_conserve(plan->p, int64_t(terms), Qd, nullptr, s)) != QCOLL_OK) return st;
   return qcoll::launch_dg_contract(W, Qd, C, n_elem, K, R, long(n3), s);
@@ -374,7 +375,8 @@ qcoll_status qcoll_dg_collide_collocated(qcoll_plan plan, int64_t n_elem, int32_
     return fail(QCOLL_EINVAL, "C must not overlap F");
   for (int k = 0; k < K; ++k)
     if (!std::isfinite(host_w[k])) return fail(QCOLL_EINVAL, "collocation weights must be finite");
-  if (!ws || ws_bytes < qcoll_dg_collocated_workspace_bytes(plan, n_elem, K))
+  const qcoll::Layout lay = qcoll::make_layout(plan->p, items, 0, 0, ws_bytes > 512 ? ws_bytes - 512 : 0);
+  if (!ws || ws_bytes < 512 + lay.total)
     return fail(QCOLL_EWORKSPACE, "workspace missing or smaller than qcoll_dg_collocated_workspace_bytes");
   qcoll_status st = check_device(plan->p);
   if (st != QCOLL_OK) return st;
@@ -385,7 +387,6 @@ qcoll_status qcoll_dg_collide_collocated(qcoll_plan plan, int64_t n_elem, int32_
   hipLaunchKernelGGL(k_fill_weights, dim3(1), dim3(64), 0, s, wt, int(K), wd);
   if (hipGetLastError() != hipSuccess) return fail(QCOLL_EDEVICE, "weight fill launch failed");
   void *ews = static_cast<char *>(ws) + 512;
-  const qcoll::Layout lay = qcoll::make_layout(plan->p, items, 0);
   // Q of every (element, node) straight from F (T = I: no contraction), stored
   // scaled by its node weight (W diagonal), or projected first and scaled by
   // the projection (it is linear, so it commutes with the weight)

@@ -34,13 +34,22 @@ namespace qcoll {
 // transposes run backwards), weighted by alpha_pq(k) and accumulated as a
 // half spectrum (planes k1 <= N/2) in registers; the weights carry w_p w_q,
 // so the multiplier is not scaled by sqrt(w_q).  The epilogue stores that sum.
-template <int N, bool VSS>
+//
+// Launches of a few pairs leave most CUs idle while each workgroup runs its M
+// terms one after the other.  There the same stages run in three launches
+// (launch_terms below): MODE 1, a workgroup per (pair, q), stores its u as
+// [j3][j1][j2] (term 0: its product, where A_p goes); k_gain_acc adds the terms
+// to A_p with the term loop's operations in its order; MODE 2 is the closing
+// stage from A_p (in the pair's own slot of W, which it then overwrites).  The
+// results are the same bits as MODE 0's, the whole loop in one workgroup.
+template <int N, bool VSS, int MODE>
 __global__ __launch_bounds__(FusedGeom<N>::NL, FusedGeom<N>::WPE) void k_gain_fused(const cplx<float> *__restrict__ H,
                                                                  const cplx<float> *__restrict__ phase,
                                                                  const float *__restrict__ wq,
                                                                  const float *__restrict__ alpha_eff,
                                                                  const float *__restrict__ apq,
-                                                                 cplx<float> *__restrict__ W, long nbp, int M,
+                                                                 cplx<float> *__restrict__ W,
+                                                                 cplx<float> *__restrict__ U, long nbp, int M,
                                                                  int Nr, float scale) {
   using G = FusedGeom<N>;
   constexpr int PPL = G::PPL, NL = G::NL;
@@ -57,8 +66,9 @@ __global__ __launch_bounds__(FusedGeom<N>::NL, FusedGeom<N>::WPE) void k_gain_fu
   const long nb = gridDim.x;
   const long full = nb / 8, rem = nb % 8;
   const long x = blockIdx.x % 8;
-  const long bp = x * full + (x < rem ? x : rem) + blockIdx.x / 8;
-  if (bp >= nbp) return;  // uniform per workgroup
+  const long lb = x * full + (x < rem ? x : rem) + blockIdx.x / 8;
+  if (lb >= (MODE == 1 ? nbp * M : nbp)) return;  // uniform per workgroup
+  const long bp = MODE == 1 ? lb / M : lb;
   const long b = bp / Nr;
   const int p = int(bp % Nr);
 
@@ -78,7 +88,14 @@ __global__ __launch_bounds__(FusedGeom<N>::NL, FusedGeom<N>::WPE) void k_gain_fu
 
   float acc[PPL][NACC];
   static_for<0, PPL>([&](auto u) {
-    static_for<0, NACC>([&](auto j) { acc[decltype(u)::value][decltype(j)::value] = 0.f; });
+    static_for<0, NACC>([&](auto j) {
+      constexpr int jj = decltype(j)::value;
+      if constexpr (MODE == 2)
+        acc[decltype(u)::value][jj] =
+            reinterpret_cast<const float *>(W + bp * (long(H1) * n2))[jj * n2 + lane + decltype(u)::value * NL];
+      else
+        acc[decltype(u)::value][jj] = 0.f;
+    });
   });
   auto wa1 = [&](int u, int i) { return i * S1 + hi[u] * N + lo[u]; };
   auto ra1 = [&](int u, int i) { return hi[u] * S1 + i * N + lo[u]; };
@@ -86,7 +103,9 @@ __global__ __launch_bounds__(FusedGeom<N>::NL, FusedGeom<N>::WPE) void k_gain_fu
   auto ra2 = [&](int u, int i) { return hi[u] * S1 + i * (N + 1) + lo[u]; };
 
   const __amdgpu_buffer_rsrc_t hr = make_rsrc(H + b * n3, unsigned(n3 * sizeof(cplx<float>)));
-  for (int q = 0; q < M; ++q) {
+  const int q0 = MODE == 1 ? int(lb % M) : 0;
+  const int q1 = MODE == 1 ? q0 + 1 : (MODE == 2 ? 0 : M);
+  for (int q = q0; q < q1; ++q) {
     const cplx<float> *ph = phase + size_t(p * M + q) * 3 * N;
     float zr[PPL][N], zi[PPL][N];
     // stage A: lane (k2, k3) = (hi, lo); c(k1) = Re(b1 b23) + Im(b1 b23),
@@ -168,7 +187,26 @@ __global__ __launch_bounds__(FusedGeom<N>::NL, FusedGeom<N>::WPE) void k_gain_fu
       lds_transpose<N, PPL>(lds, zr, wa2, ra2);
       lds_transpose<N, PPL>(lds, zi, wa2, ra2);
     }
-    if constexpr (!VSS) {
+    if constexpr (MODE == 1) {
+      static_for<0, PPL>([&](auto uu) {
+        constexpr int u = decltype(uu)::value;
+        fft_reg<N, +1, float>(zr[u], zi[u]);
+        if (q == 0) {
+          float *ao = reinterpret_cast<float *>(W + bp * (long(H1) * n2)) + lane + u * NL;
+          static_for<0, N>([&](auto j) {
+            constexpr int jj = decltype(j)::value;
+            ao[jj * n2] = __builtin_fmaf(-zi[u][jj], zi[u][jj], zr[u][jj] * zr[u][jj]);
+          });
+        } else {
+          cplx<float> *uo = U + (bp * (M - 1) + q - 1) * n3 + lane + u * NL;
+          static_for<0, N>([&](auto j) {
+            constexpr int jj = decltype(j)::value;
+            uo[jj * n2] = cplx<float>{zr[u][jj], zi[u][jj]};
+          });
+        }
+      });
+      return;
+    } else if constexpr (!VSS) {
       static_for<0, PPL>([&](auto uu) {
         constexpr int u = decltype(uu)::value;
         fft_reg<N, +1, float>(zr[u], zi[u]);
@@ -244,7 +282,7 @@ __global__ __launch_bounds__(FusedGeom<N>::NL, FusedGeom<N>::WPE) void k_gain_fu
       hi[decltype(u)::value] = t / N;
       lo[decltype(u)::value] = t % N;
     });
-    if constexpr (G::WAVE_BC) __syncthreads();
+    if constexpr (G::WAVE_BC && MODE == 0) __syncthreads();
     float zr[PPL][N], zi[PPL][N];
     static_for<0, PPL>([&](auto uu) {
       constexpr int u = decltype(uu)::value;
@@ -280,22 +318,44 @@ __global__ __launch_bounds__(FusedGeom<N>::NL, FusedGeom<N>::WPE) void k_gain_fu
   }
 }
 
-template <int N, bool VSS>
-static qcoll_status launch_fused(const Plan &p, const cplx<float> *H, cplx<float> *W, long nbp, hipStream_t st) {
+// A_p += Re(u_q)^2 - Im(u_q)^2, q = 1..M-1, from the volumes u_q that MODE 1
+// stored (they carry sqrt(w_q)): two points per lane, the operations and their
+// order those of the term loop
+__global__ __launch_bounds__(256) void k_gain_acc(const float4 *__restrict__ U, float2 *__restrict__ A, long npt,
+                                                  long nbp, long slot, int nq) {
+  const long i = long(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= nbp * npt) return;
+  const long bp = i / npt, o = i % npt;
+  const float4 *u = U + bp * nq * npt + o;
+  float2 a = A[bp * slot + o];
+#pragma unroll 6
+  for (int q = 0; q < nq; ++q) {
+    const float4 v = u[q * npt];
+    a.x = __builtin_fmaf(v.x, v.x, a.x);
+    a.x = __builtin_fmaf(-v.y, v.y, a.x);
+    a.y = __builtin_fmaf(v.z, v.z, a.y);
+    a.y = __builtin_fmaf(-v.w, v.w, a.y);
+  }
+  A[bp * slot + o] = a;
+}
+
+template <int N, bool VSS, int MODE = 0>
+static qcoll_status launch_fused(const Plan &p, const cplx<float> *H, cplx<float> *W, cplx<float> *U, long nbp,
+                                 hipStream_t st) {
   using G = FusedGeom<N>;
   // the LDS tile exceeds the default dynamic limit at N = 32; set per call
   // (cheap) so that every device the process uses gets the attribute
-  if (hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gain_fused<N, VSS>),
+  if (hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gain_fused<N, VSS, MODE>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, int(G::lds_bytes)) != hipSuccess) {
     set_error("hipFuncSetAttribute failed for the fused gain kernel");
     return QCOLL_EDEVICE;
   }
-  TimedLaunch tl("gain fused", st);
+  TimedLaunch tl(MODE == 0 ? "gain fused" : (MODE == 1 ? "gain terms" : "gain close"), st);
   const float scale = float(1.0 / double(long(N) * N * N));
-  hipLaunchKernelGGL((k_gain_fused<N, VSS>), dim3(unsigned(nbp)), dim3(G::NL), G::lds_bytes, st, H,
-                     reinterpret_cast<const cplx<float> *>(p.phase), reinterpret_cast<const float *>(p.wq),
-                     reinterpret_cast<const float *>(p.alpha_eff), reinterpret_cast<const float *>(p.alpha_pq), W,
-                     nbp, p.M, p.N_rho, scale);
+  hipLaunchKernelGGL((k_gain_fused<N, VSS, MODE>), dim3(unsigned(MODE == 1 ? nbp * p.M : nbp)), dim3(G::NL),
+                     G::lds_bytes, st, H, reinterpret_cast<const cplx<float> *>(p.phase),
+                     reinterpret_cast<const float *>(p.wq), reinterpret_cast<const float *>(p.alpha_eff),
+                     reinterpret_cast<const float *>(p.alpha_pq), W, U, nbp, p.M, p.N_rho, scale);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
     set_error(std::string("gain fused: ") + hipGetErrorString(e));
@@ -304,24 +364,48 @@ static qcoll_status launch_fused(const Plan &p, const cplx<float> *H, cplx<float
   return QCOLL_OK;
 }
 
+// one workgroup per (pair, sphere point); U holds nbp * (M - 1) complex volumes
 template <int N>
-static qcoll_status launch_fused_any(const Plan &p, const cplx<float> *H, cplx<float> *W, long nbp, hipStream_t st) {
-  return p.is_vss() ? launch_fused<N, true>(p, H, W, nbp, st) : launch_fused<N, false>(p, H, W, nbp, st);
+static qcoll_status launch_terms(const Plan &p, const cplx<float> *H, cplx<float> *W, cplx<float> *U, long nbp,
+                                 hipStream_t st) {
+  qcoll_status s = launch_fused<N, false, 1>(p, H, W, U, nbp, st);
+  if (s != QCOLL_OK) return s;
+  {
+    TimedLaunch tl("gain acc", st);
+    constexpr long npt = long(N) * N * N / 2, slot = long(N / 2 + 1) * N * N;   // float4 of u, float2 of a slot of W
+    hipLaunchKernelGGL(k_gain_acc, dim3(unsigned((nbp * npt + 255) / 256)), dim3(256), 0, st,
+                       reinterpret_cast<const float4 *>(U), reinterpret_cast<float2 *>(W), npt, nbp, slot, p.M - 1);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) {
+      set_error(std::string("gain acc: ") + hipGetErrorString(e));
+      return QCOLL_EDEVICE;
+    }
+  }
+  return launch_fused<N, false, 2>(p, H, W, U, nbp, st);
+}
+
+template <int N>
+static qcoll_status launch_fused_any(const Plan &p, const cplx<float> *H, cplx<float> *W, cplx<float> *U, long nbp,
+                                     hipStream_t st) {
+  if (p.is_vss()) return launch_fused<N, true>(p, H, W, U, nbp, st);
+  if (U) return launch_terms<N>(p, H, W, U, nbp, st);
+  return launch_fused<N, false>(p, H, W, U, nbp, st);
 }
 
 bool fused_gain_supported(int N, int precision) {
   return precision == QCOLL_FP32 && (N == 8 || N == 12 || N == 16 || N == 24 || N == 32);
 }
 
-qcoll_status launch_gain_fused(const Plan &p, const void *H, void *W, long nbp, hipStream_t st) {
+qcoll_status launch_gain_fused(const Plan &p, const void *H, void *W, void *U, long nbp, hipStream_t st) {
   const auto *h = static_cast<const cplx<float> *>(H);
   auto *a = static_cast<cplx<float> *>(W);
+  auto *u = static_cast<cplx<float> *>(U);
   switch (p.N) {
-    case 8: return launch_fused_any<8>(p, h, a, nbp, st);
-    case 12: return launch_fused_any<12>(p, h, a, nbp, st);
-    case 16: return launch_fused_any<16>(p, h, a, nbp, st);
-    case 24: return launch_fused_any<24>(p, h, a, nbp, st);
-    case 32: return launch_fused_any<32>(p, h, a, nbp, st);
+    case 8: return launch_fused_any<8>(p, h, a, u, nbp, st);
+    case 12: return launch_fused_any<12>(p, h, a, u, nbp, st);
+    case 16: return launch_fused_any<16>(p, h, a, u, nbp, st);
+    case 24: return launch_fused_any<24>(p, h, a, u, nbp, st);
+    case 32: return launch_fused_any<32>(p, h, a, u, nbp, st);
     default: set_error("fused gain kernel: unsupported N"); return QCOLL_ENOTSUP;
   }
 }

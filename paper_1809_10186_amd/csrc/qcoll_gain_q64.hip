@@ -109,20 +109,25 @@ __device__ __forceinline__ void q64_stage1(const cplx<double> *__restrict__ hb, 
   });
 }
 
-template <int N>
+// TERM = true (launches of a few pairs, which leave most CUs idle while each
+// workgroup runs its M terms one after the other): a workgroup per (pair,
+// class, q) stores its u in U, laid out as A_p (term 0: its product, in A);
+// k_gain_acc64 then adds the terms to A_p with the same operations in the same
+// order.
+template <int N, bool TERM>
 __global__ __launch_bounds__(Q64Geom<N>::NL, 2) void k_gain_q64(const cplx<double> *__restrict__ H,
                                                                 const cplx<double> *__restrict__ phase,
                                                                 const double *__restrict__ wq,
-                                                                double *__restrict__ A, long nbp, int M, int Nr,
-                                                                double scale) {
+                                                                double *__restrict__ A, cplx<double> *__restrict__ U,
+                                                                long nbp, int M, int Nr, double scale) {
   using G = Q64Geom<N>;
   constexpr int N4 = G::N4, R = G::R, S = G::S;
   constexpr long n2 = long(N) * N, n3 = n2 * N;
   extern __shared__ double tile[];
 
   const long lb = xcd_block();
-  if (lb >= nbp * 4) return;  // uniform per workgroup
-  const long bp = lb / 4;
+  if (lb >= nbp * 4 * (TERM ? M : 1)) return;  // uniform per workgroup
+  const long bp = TERM ? lb / 4 / M : lb / 4;
   const int g = int(lb % 4);
   const long b = bp / Nr;
   const int p = int(bp % Nr);
@@ -142,7 +147,8 @@ __global__ __launch_bounds__(Q64Geom<N>::NL, 2) void k_gain_q64(const cplx<doubl
   double acc[N];
   static_for<0, N>([&](auto j) { acc[decltype(j)::value] = 0.0; });
   const cplx<double> *hb = H + b * n3;
-  for (int q = 0; q < M; ++q) {
+  const int q0 = TERM ? int(lb / 4 % M) : 0, q1 = TERM ? q0 + 1 : M;
+  for (int q = q0; q < q1; ++q) {
     const cplx<double> *ph = phase + size_t(p * M + q) * 3 * N;
     const double sc = scale * __builtin_sqrt(wq[q]);
     double vr[N], vi[N];
@@ -180,6 +186,16 @@ __global__ __launch_bounds__(Q64Geom<N>::NL, 2) void k_gain_q64(const cplx<doubl
     gather3(vr);
     gather3(vi);
     fft_reg<N, +1, double>(vr, vi);   // axis 1: j1 = 0..N-1
+    if constexpr (TERM) {
+      if (q > 0) {
+        cplx<double> *u = U + (bp * (M - 1) + q - 1) * n3 + long(4 * u3 + g) * N + j3;
+        static_for<0, N>([&](auto j) {
+          constexpr int jj = decltype(j)::value;
+          u[jj * n2] = cplx<double>{vr[jj], vi[jj]};
+        });
+        return;
+      }
+    }
     static_for<0, N>([&](auto j) {
       constexpr int jj = decltype(j)::value;
       acc[jj] += vr[jj] * vr[jj];
@@ -271,19 +287,21 @@ __device__ __forceinline__ void c2_stage_a(__amdgpu_buffer_rsrc_t hr, const cplx
   });
 }
 
-template <int N>
+// TERM: as for k_gain_q64, with u stored as [j3][j1][j2] (coalesced).
+template <int N, bool TERM>
 __global__ __launch_bounds__(C2Geom<N>::NL) void k_gain_c2(const cplx<double> *__restrict__ H,
                                                           const cplx<double> *__restrict__ phase,
                                                           const double *__restrict__ wq, double *__restrict__ A,
-                                                          long nbp, int M, int Nr, double scale) {
+                                                          cplx<double> *__restrict__ U, long nbp, int M, int Nr,
+                                                          double scale) {
   using Gm = C2Geom<N>;
   constexpr int NV = Gm::NV, R = Gm::R, S = Gm::S;
   constexpr long n2 = long(N) * N, n3 = n2 * N;
   extern __shared__ double tile[];
 
   const long lb = xcd_block();
-  if (lb >= nbp * 2) return;  // uniform per workgroup
-  const long bp = lb / 2;
+  if (lb >= nbp * 2 * (TERM ? M : 1)) return;  // uniform per workgroup
+  const long bp = TERM ? lb / 2 / M : lb / 2;
   const int g = int(lb % 2);
   const long b = bp / Nr;
   const int p = int(bp % Nr);
@@ -294,7 +312,8 @@ __global__ __launch_bounds__(C2Geom<N>::NL) void k_gain_c2(const cplx<double> *_
   double acc[N];
   static_for<0, N>([&](auto j) { acc[decltype(j)::value] = 0.0; });
   const __amdgpu_buffer_rsrc_t hr = make_rsrc(H + b * n3, unsigned(n3 * sizeof(cplx<double>)));
-  for (int q = 0; q < M; ++q) {
+  const int q0 = TERM ? int(lb / 2 % M) : 0, q1 = TERM ? q0 + 1 : M;
+  for (int q = q0; q < q1; ++q) {
     const cplx<double> *ph = phase + size_t(p * M + q) * 3 * N;
     const double sc = scale * __builtin_sqrt(wq[q]);
     double zr[N], zi[N];
@@ -344,6 +363,16 @@ __global__ __launch_bounds__(C2Geom<N>::NL) void k_gain_c2(const cplx<double> *_
     b_to_c(zr);
     b_to_c(zi);
     fft_reg<N, +1, double>(zr, zi);   // axis 3: lane (v, j2) holds j3 = 0..N-1
+    if constexpr (TERM) {
+      if (q > 0) {
+        cplx<double> *u = U + (bp * (M - 1) + q - 1) * n3 + (2 * vb + g) * N + cb;
+        static_for<0, N>([&](auto j) {
+          constexpr int jj = decltype(j)::value;
+          u[jj * n2] = cplx<double>{zr[jj], zi[jj]};
+        });
+        return;
+      }
+    }
     static_for<0, N>([&](auto j) {
       constexpr int jj = decltype(j)::value;
       acc[jj] += zr[jj] * zr[jj];
@@ -358,43 +387,53 @@ __global__ __launch_bounds__(C2Geom<N>::NL) void k_gain_c2(const cplx<double> *_
   });
 }
 
+// A_p += Re(u_q)^2 - Im(u_q)^2, q = 1..M-1, from the volumes TERM stored, one
+// point per lane; with N > 0 they are laid out [j3][j1][j2]
 template <int N>
-static qcoll_status launch_c2(const Plan &p, const cplx<double> *H, double *A, long nbp, hipStream_t st) {
-  using G = C2Geom<N>;
-  if (hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gain_c2<N>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, int(G::lds_bytes)) != hipSuccess) {
-    set_error("hipFuncSetAttribute failed for the FP64 gain kernel");
-    return QCOLL_EDEVICE;
+__global__ __launch_bounds__(256) void k_gain_acc64(const double2 *__restrict__ U, double *__restrict__ A, long n3,
+                                                    long nbp, int nq) {
+  const long i = long(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i >= nbp * n3) return;
+  const long bp = i / n3, o = i % n3;
+  const double2 *u = U + bp * nq * n3 + o;
+  long d = o;
+  if constexpr (N > 0) d = (o % (N * N)) * N + o / (N * N);
+  double a = A[bp * n3 + d];
+#pragma unroll 6
+  for (int q = 0; q < nq; ++q) {
+    const double2 v = u[q * n3];
+    a = __builtin_fma(v.x, v.x, a);
+    a = __builtin_fma(-v.y, v.y, a);
   }
-  TimedLaunch tl("gain c2", st);
-  const double scale = 1.0 / double(long(N) * N * N);
-  hipLaunchKernelGGL((k_gain_c2<N>), dim3(unsigned(nbp * 2)), dim3(G::NL), G::lds_bytes, st, H,
-                     reinterpret_cast<const cplx<double> *>(p.phase), reinterpret_cast<const double *>(p.wq), A,
-                     nbp, p.M, p.N_rho, scale);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) {
-    set_error(std::string("gain c2: ") + hipGetErrorString(e));
-    return QCOLL_EDEVICE;
-  }
-  return QCOLL_OK;
+  A[bp * n3 + d] = a;
 }
 
-template <int N>
-static qcoll_status launch_q64(const Plan &p, const cplx<double> *H, double *A, long nbp, hipStream_t st) {
-  using G = Q64Geom<N>;
-  if (hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gain_q64<N>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, int(G::lds_bytes)) != hipSuccess) {
+// the whole term loop per workgroup, or with U (nbp * (M - 1) volumes) a
+// workgroup per term and the sum over the terms after it
+template <int N, int CLASSES, int PERM, class Kern>
+static qcoll_status launch_onchip64(const Plan &p, Kern kern, int lanes, size_t lds, const char *what,
+                                    const cplx<double> *H, double *A, cplx<double> *U, long nbp, hipStream_t st) {
+  if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                          int(lds)) != hipSuccess) {
     set_error("hipFuncSetAttribute failed for the FP64 gain kernel");
     return QCOLL_EDEVICE;
   }
-  TimedLaunch tl("gain q64", st);
-  const double scale = 1.0 / double(long(N) * N * N);
-  hipLaunchKernelGGL((k_gain_q64<N>), dim3(unsigned(nbp * 4)), dim3(G::NL), G::lds_bytes, st, H,
-                     reinterpret_cast<const cplx<double> *>(p.phase), reinterpret_cast<const double *>(p.wq), A,
-                     nbp, p.M, p.N_rho, scale);
+  constexpr long n3 = long(N) * N * N;
+  {
+    TimedLaunch tl(what, st);
+    const double scale = 1.0 / double(n3);
+    hipLaunchKernelGGL(kern, dim3(unsigned(nbp * CLASSES * (U ? p.M : 1))), dim3(lanes), lds, st, H,
+                       reinterpret_cast<const cplx<double> *>(p.phase), reinterpret_cast<const double *>(p.wq), A, U,
+                       nbp, p.M, p.N_rho, scale);
+  }
+  if (U) {
+    TimedLaunch tl("gain acc", st);
+    hipLaunchKernelGGL((k_gain_acc64<PERM>), dim3(unsigned((nbp * n3 + 255) / 256)), dim3(256), 0, st,
+                       reinterpret_cast<const double2 *>(U), A, n3, nbp, p.M - 1);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
-    set_error(std::string("gain q64: ") + hipGetErrorString(e));
+    set_error(std::string(what) + ": " + hipGetErrorString(e));
     return QCOLL_EDEVICE;
   }
   return QCOLL_OK;
@@ -406,11 +445,18 @@ bool use_gain_q64(const Plan &p) {
   return p.schedule != 1 && !p.is_vss() && !p.literal && gain_q64_supported(p.N, p.precision);
 }
 
-qcoll_status launch_gain_q64(const Plan &p, const void *H, double *A, long nbp, hipStream_t st) {
+qcoll_status launch_gain_q64(const Plan &p, const void *H, double *A, void *U, long nbp, hipStream_t st) {
   const auto *h = static_cast<const cplx<double> *>(H);
+  auto *u = static_cast<cplx<double> *>(U);
+  using G16 = Q64Geom<16>;
+  using G32 = C2Geom<32>;
   switch (p.N) {
-    case 16: return launch_q64<16>(p, h, A, nbp, st);
-    case 32: return launch_c2<32>(p, h, A, nbp, st);
+    case 16:
+      return launch_onchip64<16, 4, 0>(p, u ? &k_gain_q64<16, true> : &k_gain_q64<16, false>, G16::NL,
+                                       G16::lds_bytes, "gain q64", h, A, u, nbp, st);
+    case 32:
+      return launch_onchip64<32, 2, 32>(p, u ? &k_gain_c2<32, true> : &k_gain_c2<32, false>, G32::NL,
+                                        G32::lds_bytes, "gain c2", h, A, u, nbp, st);
     default: set_error("FP64 on-chip gain kernel: unsupported N"); return QCOLL_ENOTSUP;
   }
 }

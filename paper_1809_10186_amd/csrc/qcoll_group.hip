@@ -277,8 +277,8 @@ static std::vector<int> tune_chunks(int64_t batch) {
   return out;
 }
 
-size_t qcoll_autotune_workspace_bytes(qcoll_plan plan, int64_t batch) {
-  if (!plan || batch <= 0) return 0;
+// the largest candidate layout, with optional parts as far as ws_bytes holds them
+static size_t autotune_bytes(qcoll_plan plan, int64_t batch, size_t ws_bytes) {
   qcoll::Plan p = plan->p;  // copy: only schedule/chunk are varied
   size_t mx = 0;
   for (int sch : {1, 2})
@@ -286,9 +286,14 @@ size_t qcoll_autotune_workspace_bytes(qcoll_plan plan, int64_t batch) {
       if (sch == 2 && !qcoll::onchip_schedule_supported(p)) continue;
       p.schedule = sch;
       p.chunk = ck;
-      mx = std::max(mx, qcoll::make_layout(p, batch, 0).total);
+      mx = std::max(mx, qcoll::make_layout(p, batch, 0, 0, ws_bytes).total);
     }
   return mx;
+}
+
+size_t qcoll_autotune_workspace_bytes(qcoll_plan plan, int64_t batch) {
+  if (!plan || batch <= 0) return 0;
+  return autotune_bytes(plan, batch, ~size_t(0));
 }
 
 // Cache entries carry the schedule set they were timed against ("s2": the FP32
@@ -309,7 +314,7 @@ static std::string tune_key(const qcoll::Plan &p, int64_t batch) {
 qcoll_status qcoll_autotune(qcoll_plan plan, int64_t batch, const double *f, double *Q, void *ws, size_t ws_bytes,
                             void *stream, int32_t *host_schedule, int32_t *host_chunk) {
   if (!plan || batch <= 0 || !f || !Q) return gfail(QCOLL_EINVAL, "bad arguments");
-  if (!ws || ws_bytes < qcoll_autotune_workspace_bytes(plan, batch))
+  if (!ws || ws_bytes < autotune_bytes(plan, batch, ws_bytes))
     return gfail(QCOLL_EWORKSPACE, "workspace smaller than qcoll_autotune_workspace_bytes");
   qcoll::Plan &p = plan->p;
   const std::string key = tune_key(p, batch);
@@ -355,7 +360,7 @@ qcoll_status qcoll_autotune(qcoll_plan plan, int64_t batch, const double *f, dou
       if (sch == 2 && !qcoll::onchip_schedule_supported(p)) continue;
       p.schedule = sch;
       p.chunk = ck;
-      const qcoll::Layout lay = qcoll::make_layout(p, batch, 0);
+      const qcoll::Layout lay = qcoll::make_layout(p, batch, 0, 0, ws_bytes);
       if ((rc = qcoll::launch_eval(p, batch, f, Q, ws, lay, st)) != QCOLL_OK) break;  // warm-up
       // best of two timed runs
       float ms = 1e30f;
@@ -394,18 +399,22 @@ qcoll_status qcoll_autotune(qcoll_plan plan, int64_t batch, const double *f, dou
   return QCOLL_OK;
 }
 
-size_t qcoll_group_autotune_workspace_bytes(qcoll_group g) {
-  if (!g) return 0;
+static size_t group_autotune_bytes(qcoll_group g, size_t ws_bytes) {
   size_t mx = 0;
   for (size_t i = 0; i < g->plans.size(); ++i)
-    if (g->counts[i] > 0) mx = std::max(mx, qcoll_autotune_workspace_bytes(g->plans[i], g->counts[i]));
+    if (g->counts[i] > 0) mx = std::max(mx, autotune_bytes(g->plans[i], g->counts[i], ws_bytes));
   return mx;
+}
+
+size_t qcoll_group_autotune_workspace_bytes(qcoll_group g) {
+  if (!g) return 0;
+  return group_autotune_bytes(g, ~size_t(0));
 }
 
 qcoll_status qcoll_group_autotune(qcoll_group g, const double *const *f, double *const *Q, void *ws, size_t ws_bytes,
                                   void *stream) {
   if (!g || !f || !Q) return gfail(QCOLL_EINVAL, "NULL argument");
-  if (!ws || ws_bytes < qcoll_group_autotune_workspace_bytes(g))
+  if (!ws || ws_bytes < group_autotune_bytes(g, ws_bytes))
     return gfail(QCOLL_EWORKSPACE, "workspace smaller than qcoll_group_autotune_workspace_bytes");
   for (size_t i = 0; i < g->plans.size(); ++i) {
     if (g->counts[i] == 0) continue;

@@ -74,11 +74,16 @@ struct Layout {
   size_t off_yh = 0;                                    // two-pass VSS vjp: paired h_pq volumes
   size_t off_vp = 0;                                    // two-pass VSS eval: partial half spectra
   size_t off_hg = 0, off_h64g = 0, off_yg = 0;          // bilinear extras
+  size_t off_u = 0;     // eval of a few items: per-term volumes of the on-chip gain kernels (u_pairs > 0)
+  long u_pairs = 0;     // pairs whose M - 1 volumes fit there
   size_t total = 0;
 };
 
-// chunk > 0 overrides the plan's items per eval chunk (op 0 and 2)
-Layout make_layout(const Plan &p, int64_t batch, int op, long chunk = 0);
+// chunk > 0 overrides the plan's items per eval chunk (op 0 and 2); ws_bytes:
+// the workspace at hand (optional parts are left out where they do not fit)
+Layout make_layout(const Plan &p, int64_t batch, int op, long chunk = 0, size_t ws_bytes = ~size_t(0));
+// the on-chip gain loop of nbp pairs is faster as one workgroup per term
+bool split_terms(const Plan &p, long nbp);
 
 // isc: optional device array of K per-item weights; item i of the call is
 // stored scaled by isc[i % K] (the collocated DG weak form)
@@ -100,11 +105,12 @@ qcoll_status launch_dg_contract(const double *A, const double *X, double *Y, lon
                                 hipStream_t st);
 bool fused_gain_supported(int N, int precision);
 bool use_fused_gain(const Plan &p);
-qcoll_status launch_gain_fused(const Plan &p, const void *H, void *W, long nbp, hipStream_t st);
-// FP64 gain loop on chip (N = 16): A_p of every (item, node) pair
+// U: nbp * (M - 1) complex volumes (one workgroup per term), or null (one per pair)
+qcoll_status launch_gain_fused(const Plan &p, const void *H, void *W, void *U, long nbp, hipStream_t st);
+// FP64 gain loop on chip (N = 16, 32): A_p of every (item, node) pair; U as above
 bool gain_q64_supported(int N, int precision);
 bool use_gain_q64(const Plan &p);
-qcoll_status launch_gain_q64(const Plan &p, const void *H, double *A, long nbp, hipStream_t st);
+qcoll_status launch_gain_q64(const Plan &p, const void *H, double *A, void *U, long nbp, hipStream_t st);
 // schedule 2 exists for this grid and precision (FP32 fused kernel or FP64 on-chip gain)
 inline bool onchip_schedule_supported(int N, int precision) {
   return fused_gain_supported(N, precision) || gain_q64_supported(N, precision);

@@ -7,6 +7,7 @@
 //     the last passes.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdio>
 #include <type_traits>
 
@@ -792,11 +793,11 @@ struct Engine {
   }
 
   // A[b][p] for items of this chunk: (b, p) pairs bp in [0, nb*Nr)
-  static qcoll_status gain_terms(const Plan &p, const C<T> *H, T *A, C<T> *Y, long nb, long pc,
+  static qcoll_status gain_terms(const Plan &p, const C<T> *H, T *A, C<T> *Y, C<T> *U, long nb, long pc,
                                  hipStream_t st) {
     const long nbp = nb * p.N_rho;
     if constexpr (std::is_same<T, double>::value) {
-      if (use_gain_q64(p)) return launch_gain_q64(p, H, A, nbp, st);
+      if (use_gain_q64(p)) return launch_gain_q64(p, H, A, U, nbp, st);
     }
     const T scale = T(1.0 / double(n3));
     for (long bp0 = 0; bp0 < nbp; bp0 += pc) {
@@ -856,7 +857,7 @@ struct Engine {
     qcoll_status s;
     // FP32 with N <= 32: the whole per-pair loop on chip (fused kernel, VSS mode)
     const bool fused = std::is_same<T, float>::value && use_fused_gain(p) && !Hg;
-    if (fused && (s = launch_gain_fused(p, H, Wp, nbp, st))) return s;
+    if (fused && (s = launch_gain_fused(p, H, Wp, nullptr, nbp, st))) return s;
     for (long bp0 = 0; !fused && bp0 < nbp; bp0 += pc) {
       const long cnt = (nbp - bp0 < pc) ? (nbp - bp0) : pc;
       SrcShift<T, N> src{H, reinterpret_cast<const C<T> *>(p.phase), bp0, p.M, p.N_rho, scale};
@@ -967,6 +968,8 @@ struct Engine {
     for (long b0 = 0; b0 < batch; b0 += lay.bc) {
       const long nb = (batch - b0 < lay.bc) ? (batch - b0) : lay.bc;
       const double *fb = f + b0 * n3;
+      C<T> *U = (lay.u_pairs >= nb * p.N_rho && split_terms(p, nb * p.N_rho))
+                    ? reinterpret_cast<C<T> *>(w + lay.off_u) : nullptr;
       qcoll_status s;
       // spectrum of f in FP64 (shared by the gain and the loss), and its copy
       // in the working precision for the gain
@@ -998,7 +1001,7 @@ struct Engine {
         if (use_fused_gain(p)) {
           // gain terms and the low-rank stage on chip; W[b][p] = alpha_p fft3(A_p)
           C<T> *Wp = reinterpret_cast<C<T> *>(A);
-          if ((s = launch_gain_fused(p, H, Wp, nb * p.N_rho, st))) return s;
+          if ((s = launch_gain_fused(p, H, Wp, U, nb * p.N_rho, st))) return s;
           // half spectra from here on: planes k1 <= N/2 of every item
           constexpr long nh = long(N / 2 + 1) * N * N;
           constexpr int H1 = N / 2 + 1;
@@ -1021,9 +1024,9 @@ struct Engine {
             return s;
           continue;
         }
-        if ((s = gain_terms(p, H, A, Y, nb, lay.pc, st))) return s;
+        if ((s = gain_terms(p, H, A, Y, U, nb, lay.pc, st))) return s;
       } else {
-        if ((s = gain_terms(p, H, A, Y, nb, lay.pc, st))) return s;
+        if ((s = gain_terms(p, H, A, Y, U, nb, lay.pc, st))) return s;
       }
       const T *Bsrc = A;
       if (!p.mix_identity) {
@@ -1230,7 +1233,33 @@ bool use_fused_gain(const Plan &p) {
   return p.schedule != 1 && !p.literal && fused_gain_supported(p.N, p.precision);
 }
 
-Layout make_layout(const Plan &p, int64_t batch, int op, long chunk) {
+// One workgroup per (pair, term) instead of one per pair: the terms run side by
+// side, at the price of their volumes going through memory (written once, read
+// once) and one or two launches more.  In microseconds: t a term of a workgroup
+// (measured), slots the workgroups the chip holds, wgs those of a pair, u a
+// volume's way through memory at the 7 TB/s that these cache-sized passes reach.
+// Measured, whole call of one item with N_rho = 16 and M = 12, one workgroup per
+// pair against per term: FP32 12^3 42 -> 28 us, 16^3 52 -> 33, 24^3 124 -> 61,
+// 32^3 156 -> 74 (two items 158 -> 95, three 159 -> 121, and level at four);
+// FP64 16^3 107 -> 54, 32^3 212 -> 121.  At 8^3 the launches cost what it gains.
+bool split_terms(const Plan &p, long nbp) {
+  if (p.is_vss() || p.M < 2 || !(use_fused_gain(p) || use_gain_q64(p))) return false;
+  const bool dp = p.precision == QCOLL_FP64;
+  double t, slots, wgs = 1.0;
+  switch (p.N) {
+    case 12: t = 2.0; slots = 1024; break;
+    case 16: t = dp ? 6.5 : 2.5; slots = dp ? 2048 : 1024; wgs = dp ? 4.0 : 1.0; break;
+    case 24: t = 7.5; slots = 512; break;
+    case 32: t = dp ? 12.0 : 9.5; slots = 256; wgs = dp ? 2.0 : 1.0; break;
+    default: return false;
+  }
+  const double u = 2.0 * p.n3() * (dp ? 16.0 : 8.0) / 7.0e6;
+  const double n = double(nbp) * p.M;
+  if (wgs * nbp > slots / 2) return false;
+  return std::ceil(wgs * n / slots) * t + n * u + 8.0 < t * p.M;
+}
+
+Layout make_layout(const Plan &p, int64_t batch, int op, long chunk, size_t ws_bytes) {
   Layout l;
   const size_t es = (p.precision == QCOLL_FP32) ? sizeof(float) : sizeof(double);
   const long n3 = p.n3();
@@ -1324,6 +1353,16 @@ Layout make_layout(const Plan &p, int64_t batch, int op, long chunk) {
     l.off_hg = o; o += al(size_t(l.bc) * n3 * 2 * es);
     l.off_h64g = o; o += al(size_t(l.bc) * n3 * 2 * sizeof(double));
     l.off_yg = o; o += al(size_t(l.pc) * p.M * n3 * 2 * es);
+  }
+  if (!bil && split_terms(p, l.bc * p.N_rho)) {
+    const size_t u = al(size_t(l.bc) * p.N_rho * (p.M - 1) * n3 * 2 * es);
+    // a workspace sized for another batch may not hold them: the loop then runs
+    // in one workgroup per pair (the results are the same bits)
+    if (o + u <= ws_bytes) {
+      l.off_u = o;
+      l.u_pairs = l.bc * p.N_rho;
+      o += u;
+    }
   }
   l.total = o;
   return l;

@@ -63,20 +63,20 @@ extern "C" qcoll_status qcoll_eval_noalloc(qcoll_plan plan, int64_t batch, const
   // items per chunk: the plan's chunk (default 64), reduced until one chunk's
   // workspace fits the array (the workspace grows with the chunk)
   const long want = std::min<long>(batch, p.chunk > 0 ? p.chunk : 64);
-  if (qcoll::make_layout(p, batch, 0, 1).total > kScratchBytes)
+  if (qcoll::make_layout(p, batch, 0, 1, 0).total > kScratchBytes)
     return nfail(QCOLL_EWORKSPACE, "one item of this plan needs " +
-                                       std::to_string(qcoll::make_layout(p, batch, 0, 1).total) +
+                                       std::to_string(qcoll::make_layout(p, batch, 0, 1, 0).total) +
                                        " bytes of scratch; qcoll_eval_noalloc holds " +
                                        std::to_string(kScratchBytes) + " (use qcoll_eval with a workspace)");
   long lo = 1, hi = want;   // largest chunk in [1, want] that fits
   while (lo < hi) {
     const long mid = (lo + hi + 1) / 2;
-    if (qcoll::make_layout(p, batch, 0, mid).total <= kScratchBytes) lo = mid;
+    if (qcoll::make_layout(p, batch, 0, mid, 0).total <= kScratchBytes) lo = mid;
     else hi = mid - 1;
   }
   void *ws = nullptr;
   qcoll_status st = scratch_ptr(dev, &ws);
   if (st != QCOLL_OK) return st;
-  const qcoll::Layout lay = qcoll::make_layout(p, batch, 0, lo);
+  const qcoll::Layout lay = qcoll::make_layout(p, batch, 0, lo, kScratchBytes);
   return qcoll::launch_eval(p, batch, f, Q, ws, lay, static_cast<hipStream_t>(stream));
 }
