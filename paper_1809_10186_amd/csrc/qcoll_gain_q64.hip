@@ -43,24 +43,24 @@ struct Q64Geom {
   static constexpr size_t lds_bytes = size_t(N) * S * sizeof(double);
   // the stage-2 transpose stays inside a wave when the N/4 lanes of a k1 do
   static constexpr bool WAVE2 = (64 % N4 == 0);
-  // rows of stage-1 loads in flight (4 pencils each): the outputs and the
-  // accumulator hold most of the register budget
-  static constexpr int KG = 2;
+  // rows of stage-1 loads in flight (4 pencils each)
+  static constexpr int KG = 4;
 };
 
 // stage 1 for residue class G: v[m N/4 + u] = X_m[4u + G], X_m the inverse
 // transform along axis 2 of pencil (k1, t + m N/4) of c_s f^
 template <int N, int G>
-__device__ __forceinline__ void q64_stage1(const cplx<double> *__restrict__ hb, const cplx<double> *__restrict__ ph,
-                                           int k1, int t, double sc, double *vr, double *vi) {
+__device__ __forceinline__ void q64_stage1(__amdgpu_buffer_rsrc_t hr, const cplx<double> *__restrict__ ph, int k1,
+                                           int t, double sc, double *vr, double *vi) {
   constexpr int N4 = N / 4, KG = Q64Geom<N>::KG;
+  const int vo = int((k1 * N * N + t) * sizeof(cplx<double>));
   const cplx<double> b1 = ph[k1];
   double P[4], Qm[4];
   static_for<0, 4>([&](auto mm) {
     constexpr int m = decltype(mm)::value;
     const cplx<double> b3 = ph[2 * N + t + N4 * m];
-    const double xr = b1.re * b3.re - b1.im * b3.im;
-    const double xi = b1.re * b3.im + b1.im * b3.re;
+    const double xr = __builtin_fma(b1.re, b3.re, -(b1.im * b3.im));
+    const double xi = __builtin_fma(b1.re, b3.im, b1.im * b3.re);
     // Re(b1 b2 b3) + Im(b1 b2 b3) = b2.re P + b2.im Qm
     P[m] = (xr + xi) * sc;
     Qm[m] = (xr - xi) * sc;
@@ -69,34 +69,44 @@ __device__ __forceinline__ void q64_stage1(const cplx<double> *__restrict__ hb, 
     vr[decltype(j)::value] = 0.0;
     vi[decltype(j)::value] = 0.0;
   });
-  // k2 outer (each b2 serves the four pencils), KG rows of loads in flight at
-  // a time (scheduling barriers): the outputs and the accumulator already hold
-  // most of the register budget
-  static_for<0, N>([&](auto kk) {
-    constexpr int k2 = decltype(kk)::value;
-    constexpr int a = k2 / N4, bb = k2 % N4;
-    constexpr int e = (G * a) & 3;   // y_b += i^e c x
-    if constexpr (k2 % KG == 0) __builtin_amdgcn_sched_barrier(0);
-    const cplx<double> b2 = ph[N + k2];
-    static_for<0, 4>([&](auto mm) {
-      constexpr int m = decltype(mm)::value;
-      constexpr int o = m * N4 + bb;
-      const cplx<double> h = hb[(long(k1) * N + k2) * N + t + N4 * m];
-      const double c = b2.re * P[m] + b2.im * Qm[m];
-      if constexpr (e == 0) {
-        vr[o] += h.re * c;
-        vi[o] += h.im * c;
-      } else if constexpr (e == 1) {
-        vr[o] -= h.im * c;
-        vi[o] += h.re * c;
-      } else if constexpr (e == 2) {
-        vr[o] -= h.re * c;
-        vi[o] -= h.im * c;
-      } else {
-        vr[o] += h.im * c;
-        vi[o] -= h.re * c;
-      }
+  // k2 outer (each b2 serves the four pencils); the loads of KG rows are issued
+  // together before their arithmetic
+  static_for<0, N / KG>([&](auto gg) {
+    constexpr int g0 = decltype(gg)::value * KG;
+    cplx<double> v[KG][4];
+    static_for<0, KG>([&](auto ii) {
+      static_for<0, 4>([&](auto mm) {
+        v[decltype(ii)::value][decltype(mm)::value] =
+            load_c64(hr, vo, int(((g0 + decltype(ii)::value) * N + N4 * decltype(mm)::value) * sizeof(cplx<double>)));
+      });
     });
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<0, KG>([&](auto ii) {
+      constexpr int k2 = g0 + decltype(ii)::value;
+      constexpr int a = k2 / N4, bb = k2 % N4;
+      constexpr int e = (G * a) & 3;   // y_b += i^e c x
+      const cplx<double> b2 = ph[N + k2];
+      static_for<0, 4>([&](auto mm) {
+        constexpr int m = decltype(mm)::value;
+        constexpr int o = m * N4 + bb;
+        const cplx<double> h = v[decltype(ii)::value][m];
+        const double c = __builtin_fma(b2.re, P[m], b2.im * Qm[m]);
+        if constexpr (e == 0) {
+          vr[o] = __builtin_fma(h.re, c, vr[o]);
+          vi[o] = __builtin_fma(h.im, c, vi[o]);
+        } else if constexpr (e == 1) {
+          vr[o] = __builtin_fma(-h.im, c, vr[o]);
+          vi[o] = __builtin_fma(h.re, c, vi[o]);
+        } else if constexpr (e == 2) {
+          vr[o] = __builtin_fma(-h.re, c, vr[o]);
+          vi[o] = __builtin_fma(-h.im, c, vi[o]);
+        } else {
+          vr[o] = __builtin_fma(h.im, c, vr[o]);
+          vi[o] = __builtin_fma(-h.re, c, vi[o]);
+        }
+      });
+    });
+    __builtin_amdgcn_sched_barrier(0);
   });
   __builtin_amdgcn_sched_barrier(0);
   static_for<0, 4>([&](auto mm) {
@@ -146,17 +156,17 @@ __global__ __launch_bounds__(Q64Geom<N>::NL, 2) void k_gain_q64(const cplx<doubl
 
   double acc[N];
   static_for<0, N>([&](auto j) { acc[decltype(j)::value] = 0.0; });
-  const cplx<double> *hb = H + b * n3;
+  const __amdgpu_buffer_rsrc_t hr = make_rsrc(H + b * n3, unsigned(n3 * sizeof(cplx<double>)));
   const int q0 = TERM ? int(lb / 4 % M) : 0, q1 = TERM ? q0 + 1 : M;
   for (int q = q0; q < q1; ++q) {
     const cplx<double> *ph = phase + size_t(p * M + q) * 3 * N;
     const double sc = scale * __builtin_sqrt(wq[q]);
     double vr[N], vi[N];
     switch (g) {
-      case 0: q64_stage1<N, 0>(hb, ph, k1, t, sc, vr, vi); break;
-      case 1: q64_stage1<N, 1>(hb, ph, k1, t, sc, vr, vi); break;
-      case 2: q64_stage1<N, 2>(hb, ph, k1, t, sc, vr, vi); break;
-      default: q64_stage1<N, 3>(hb, ph, k1, t, sc, vr, vi); break;
+      case 0: q64_stage1<N, 0>(hr, ph, k1, t, sc, vr, vi); break;
+      case 1: q64_stage1<N, 1>(hr, ph, k1, t, sc, vr, vi); break;
+      case 2: q64_stage1<N, 2>(hr, ph, k1, t, sc, vr, vi); break;
+      default: q64_stage1<N, 3>(hr, ph, k1, t, sc, vr, vi); break;
     }
     // stage 2: (k1, t) holds k3 = t + m N/4 for every u; gather all k3 of u = t.
     // The previous term's stage-3 reads cross waves: finish them first.
@@ -198,9 +208,10 @@ __global__ __launch_bounds__(Q64Geom<N>::NL, 2) void k_gain_q64(const cplx<doubl
     }
     static_for<0, N>([&](auto j) {
       constexpr int jj = decltype(j)::value;
-      acc[jj] += vr[jj] * vr[jj];
-      acc[jj] -= vi[jj] * vi[jj];
+      acc[jj] = __builtin_fma(vr[jj], vr[jj], acc[jj]);
+      acc[jj] = __builtin_fma(-vi[jj], vi[jj], acc[jj]);
     });
+    if constexpr (TERM) break;
   }
   double *a = A + bp * n3 + long(4 * u3 + g) * N + j3;
   static_for<0, N>([&](auto j) { a[decltype(j)::value * n2] = acc[decltype(j)::value]; });
@@ -228,7 +239,7 @@ struct C2Geom {
   static constexpr int NL = N * N / 2;
   static constexpr int R = N + 1;
   static constexpr int S = N * R;
-  static constexpr size_t lds_bytes = size_t(NV) * S * sizeof(double);
+  static constexpr size_t lds_bytes = (size_t(NV) * S + 4 * N) * sizeof(double);   // tile, two rows of b1
   static constexpr bool WAVE_BC = (64 % N == 0);
   // stage-A outputs whose two loads each are issued together: eight loads in
   // flight (four outputs) fit beside the accumulator and the outputs; with
@@ -239,7 +250,7 @@ struct C2Geom {
 
 template <int N, int G>
 __device__ __forceinline__ void c2_stage_a(__amdgpu_buffer_rsrc_t hr, const cplx<double> *__restrict__ ph,
-                                           int lane, double sc, double *zr, double *zi) {
+                                           const cplx<double> *b1q, int lane, double sc, double *zr, double *zi) {
   constexpr int NV = C2Geom<N>::NV, NL = C2Geom<N>::NL;
   constexpr long n2 = long(N) * N;
   static_for<0, 2>([&](auto mm) {
@@ -247,8 +258,8 @@ __device__ __forceinline__ void c2_stage_a(__amdgpu_buffer_rsrc_t hr, const cplx
     const int t = lane + m * NL;   // pencil (k2, k3) = (t / N, t % N)
     const cplx<double> b2 = ph[N + t / N], b3 = ph[2 * N + t % N];
     // c_s(k1) = Re(b1 b2 b3) + Im(b1 b2 b3) = b1.re P + b1.im Qm, times 1/N^3 sqrt(w_q)
-    const double xr = b2.re * b3.re - b2.im * b3.im;
-    const double yi = b2.re * b3.im + b2.im * b3.re;
+    const double xr = __builtin_fma(b2.re, b3.re, -(b2.im * b3.im));
+    const double yi = __builtin_fma(b2.re, b3.im, b2.im * b3.re);
     const double P = (xr + yi) * sc, Qm = (xr - yi) * sc;
     // buffer loads with the element offset as a scalar: no per-element
     // address registers to keep across the term loop.  The loads of KG
@@ -267,15 +278,15 @@ __device__ __forceinline__ void c2_stage_a(__amdgpu_buffer_rsrc_t hr, const cplx
       static_for<0, KG>([&](auto ii) {
       constexpr int b = g0 + decltype(ii)::value;
       const cplx<double> h0 = hl[decltype(ii)::value], h1 = hh[decltype(ii)::value];
-      const cplx<double> e0 = ph[b], e1 = ph[NV + b];
-      const double c0 = e0.re * P + e0.im * Qm, c1 = e1.re * P + e1.im * Qm;
+      const cplx<double> e0 = b1q[b], e1 = b1q[NV + b];
+      const double c0 = __builtin_fma(e0.re, P, e0.im * Qm), c1 = __builtin_fma(e1.re, P, e1.im * Qm);
       double yr, yim;
       if constexpr (G == 0) {
-        yr = h0.re * c0 + h1.re * c1;
-        yim = h0.im * c0 + h1.im * c1;
+        yr = __builtin_fma(h0.re, c0, h1.re * c1);
+        yim = __builtin_fma(h0.im, c0, h1.im * c1);
       } else {
-        yr = h0.re * c0 - h1.re * c1;
-        yim = h0.im * c0 - h1.im * c1;
+        yr = __builtin_fma(h0.re, c0, -(h1.re * c1));
+        yim = __builtin_fma(h0.im, c0, -(h1.im * c1));
       }
       twiddle<N, G * b, +1, double>(yr, yim);   // e^(2 pi i G b / N)
       zr[m * NV + b] = yr;
@@ -313,16 +324,28 @@ __global__ __launch_bounds__(C2Geom<N>::NL) void k_gain_c2(const cplx<double> *_
   static_for<0, N>([&](auto j) { acc[decltype(j)::value] = 0.0; });
   const __amdgpu_buffer_rsrc_t hr = make_rsrc(H + b * n3, unsigned(n3 * sizeof(cplx<double>)));
   const int q0 = TERM ? int(lb / 2 % M) : 0, q1 = TERM ? q0 + 1 : M;
+  // the axis-1 shift factors of this term and the next behind the tile: as
+  // scalar loads they overflow the scalar registers (400 of 1 876 instructions
+  // a term moved them in and out of vector lanes; read again for each pencil,
+  // the waits for them cost more than that)
+  cplx<double> *b1s = reinterpret_cast<cplx<double> *>(tile + NV * S);
+  if (lane < N) b1s[(q0 & 1) * N + lane] = phase[size_t(p * M + q0) * 3 * N + lane];
+  __syncthreads();
   for (int q = q0; q < q1; ++q) {
     const cplx<double> *ph = phase + size_t(p * M + q) * 3 * N;
     const double sc = scale * __builtin_sqrt(wq[q]);
     double zr[N], zi[N];
-    if (g == 0) c2_stage_a<N, 0>(hr, ph, lane, sc, zr, zi);
-    else c2_stage_a<N, 1>(hr, ph, lane, sc, zr, zi);
+    const cplx<double> *b1q = b1s + (q & 1) * N;
+    cplx<double> b1n{};
+    if (lane < N && q + 1 < q1) b1n = ph[3 * N + lane];
+    if (g == 0) c2_stage_a<N, 0>(hr, ph, b1q, lane, sc, zr, zi);
+    else c2_stage_a<N, 1>(hr, ph, b1q, lane, sc, zr, zi);
     // A -> B (across waves): element (v, k2, k3) at v*S + k2*R + k3.  The
     // previous term's stage-C reads stay inside each wave's own planes, so one
-    // barrier before the writes orders them against other waves' reads.
+    // barrier before the writes orders them against other waves' reads (and
+    // the next term's factors against this and the previous term's).
     __syncthreads();
+    if (lane < N && q + 1 < q1) b1s[((q + 1) & 1) * N + lane] = b1n;
     auto a_to_b = [&](double *z, bool tail) {
       static_for<0, 2>([&](auto mm) {
         constexpr int m = decltype(mm)::value;
@@ -375,9 +398,10 @@ __global__ __launch_bounds__(C2Geom<N>::NL) void k_gain_c2(const cplx<double> *_
     }
     static_for<0, N>([&](auto j) {
       constexpr int jj = decltype(j)::value;
-      acc[jj] += zr[jj] * zr[jj];
-      acc[jj] -= zi[jj] * zi[jj];
+      acc[jj] = __builtin_fma(zr[jj], zr[jj], acc[jj]);
+      acc[jj] = __builtin_fma(-zi[jj], zi[jj], acc[jj]);
     });
+    if constexpr (TERM) break;
   }
   // A_p[2v + g][j2][j3]: N consecutive doubles per lane
   double2 *a = reinterpret_cast<double2 *>(A + bp * n3 + long(2 * vb + g) * n2 + long(cb) * N);
