@@ -107,6 +107,10 @@ bool fused_gain_supported(int N, int precision);
 bool use_fused_gain(const Plan &p);
 // U: nbp * (M - 1) complex volumes (one workgroup per term), or null (one per pair)
 qcoll_status launch_gain_fused(const Plan &p, const void *H, void *W, void *U, long nbp, hipStream_t st);
+// bilinear gain loop on chip (FP32, N <= 32): A_p of the nbp pairs as
+// [j1][j2][j3]; S: cap complex volumes of scratch
+qcoll_status launch_gain_bil(const Plan &p, const void *Hf, const void *Hg, void *A, void *S, long cap, long nbp,
+                             hipStream_t st);
 // FP64 gain loop on chip (N = 16, 32): A_p of every (item, node) pair; U as above
 bool gain_q64_supported(int N, int precision);
 bool use_gain_q64(const Plan &p);

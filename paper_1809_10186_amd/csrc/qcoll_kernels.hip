@@ -778,6 +778,21 @@ struct OpLowRankC {
   }
 };
 
+// The bilinear gain loop of nbp pairs on chip: the same bits as the two passes,
+// whose time grows with the pairs, while a workgroup's is the same until the
+// chip is full.  Whole calls, on chip against two passes, M = 12: 32^3 (two
+// workgroups per pair) 64 pairs about 0.28 / 0.26 ms, 128 0.29 / 0.45, 1024
+// 1.8 / 3.0; 24^3 128 pairs 0.31 / 0.24, 256 0.37 / 0.42, 1024 1.31 / 1.50
+// (M = 6: 256 pairs 0.23 / 0.22, 512 level); 16^3 128 pairs 115 / 83 us, 256
+// 120 / 125, 1024 204 / 383; 12^3 128 pairs 90 / 73 us, 256 92 / 107; 8^3 128
+// pairs 52 / 48 us, 256 53 / 69.
+static bool use_gain_bil(const Plan &p, long nbp) {
+  if (!use_fused_gain(p)) return false;
+  if (p.N == 32) return nbp > 64;
+  if (p.N == 24) return nbp * p.M >= 3072;
+  return nbp >= 256;
+}
+
 // ----------------------------------------------------------------------------
 template <typename T, int N>
 struct Engine {
@@ -824,6 +839,10 @@ struct Engine {
                                   long pc, hipStream_t st) {
     const long nbp = nb * p.N_rho;
     const T scale = T(1.0 / double(n3));
+    if constexpr (std::is_same<T, float>::value) {
+      // on chip: scratch in Yf (pc * M volumes)
+      if (use_gain_bil(p, nbp)) return launch_gain_bil(p, Hf, Hg, A, Yf, pc * p.M, nbp, st);
+    }
     for (long bp0 = 0; bp0 < nbp; bp0 += pc) {
       const long cnt = (nbp - bp0 < pc) ? (nbp - bp0) : pc;
       qcoll_status s;
