@@ -864,7 +864,8 @@ struct Engine {
   // the half-spectrum tail of the fused schedule.
   // (Hg, H64g, Yg non-null: the bilinear Q(f, g), two-pass in both precisions)
   static qcoll_status eval_vss(const Plan &p, const C<T> *H, const C<double> *H64, T *A, C<T> *Y, C<double> *TA,
-                               C<T> *VP, C<double> *LH, const double *fb, double *Qb, long nb, long pc,
+                               C<T> *VP, C<double> *Zp, long zstride, C<double> *LH, const double *fb,
+                               double *Qb, long nb, long pc,
                                hipStream_t st, const double *isc, int K, long b0, const C<T> *Hg = nullptr,
                                const C<double> *H64g = nullptr, C<T> *Yg = nullptr) {
     constexpr int H1 = N / 2 + 1;
@@ -876,6 +877,21 @@ struct Engine {
     qcoll_status s;
     // FP32 with N <= 32: the whole per-pair loop on chip (fused kernel, VSS mode)
     const bool fused = std::is_same<T, float>::value && use_fused_gain(p) && !Hg;
+    if constexpr (std::is_same<T, double>::value && N == 32) {
+      // the terms' spectra on chip, then the full-spectrum tail (Z is not Hermitian,
+      // the gain is its real part)
+      if (use_vss_terms64(p) && !Hg) {
+        if ((s = launch_vss_terms64(p, H, Y, Zp, zstride, nb, pc, st))) return s;
+        if ((s = Passes<double, N>::template slab<SrcParts<double, N>, DstCplx<double, N>, +1>(
+                 SrcParts<double, N>{Zp, zstride}, DstCplx<double, N>{TA}, nb * N, st, "gain inverse slab")))
+          return s;
+        if ((s = Passes<double, N>::template slab<SrcLoss<N>, DstCplx<double, N>, +1>(
+                 SrcLoss<N>{H64, reinterpret_cast<const double *>(p.lam)}, DstCplx<double, N>{LH}, nb * N, st,
+                 "loss slab")))
+          return s;
+        return pencil(OpAssemble<double, N>{TA, LH, fb, Qb, isc, K, b0}, nb * N * N, st, "assemble");
+      }
+    }
     if (fused && (s = launch_gain_fused(p, H, Wp, nullptr, nbp, st))) return s;
     for (long bp0 = 0; !fused && bp0 < nbp; bp0 += pc) {
       const long cnt = (nbp - bp0 < pc) ? (nbp - bp0) : pc;
@@ -1000,7 +1016,7 @@ struct Engine {
       if constexpr (N <= 48) {   // VSS kernels: N <= 48 (the plan refuses larger grids)
         if (p.is_vss()) {
           if (g && (s = Passes<double, N>::template forward_to<T>(g + b0 * n3, H64g, Hg, nb, st))) return s;
-          if ((s = eval_vss(p, H, H64, A, Y, TA, VP, LH, fb, Q + b0 * n3, nb, lay.pc, st, isc, K, b0,
+          if ((s = eval_vss(p, H, H64, A, Y, TA, VP, reinterpret_cast<C<double> *>(w + lay.off_zp), lay.bc * n3, LH, fb, Q + b0 * n3, nb, lay.pc, st, isc, K, b0,
                             g ? Hg : nullptr, g ? H64g : nullptr, g ? Yg : nullptr)))
             return s;
           continue;
@@ -1278,6 +1294,10 @@ bool split_terms(const Plan &p, long nbp) {
   return std::ceil(wgs * n / slots) * t + n * u + 8.0 < t * p.M;
 }
 
+// items per launch of the FP64 on-chip term loops: at N_rho = 16 two workgroups
+// of every pair of 16 items fill 256 CUs twice; more only adds volumes
+constexpr long kTermItems = 16;
+
 Layout make_layout(const Plan &p, int64_t batch, int op, long chunk, size_t ws_bytes) {
   Layout l;
   const size_t es = (p.precision == QCOLL_FP32) ? sizeof(float) : sizeof(double);
@@ -1292,14 +1312,17 @@ Layout make_layout(const Plan &p, int64_t batch, int op, long chunk, size_t ws_b
     // capped at 4 GiB.
     // The fused adjoint has no sub-chunks: its chunks hold up to 256 items
     // (fewer, larger launches of the small passes around it).
-    const long cap = use_fused_adjoint(p) ? 256 : 32;
+    const bool t64 = use_adjoint_terms64(p);
+    const long cap = use_fused_adjoint(p) ? 256 : (t64 ? 64 : 32);
     l.bc = batch < cap ? (batch > 0 ? batch : 1) : cap;
     // (VSS kernels add the paired h_pq volumes, ceil(M/2) complex volumes per pair)
     const size_t per_item_y = size_t(p.N_rho) * p.M * n3 * 2 * es;
     const size_t per_item_yh = p.is_vss() ? size_t(p.N_rho) * ((p.M + 1) / 2) * n3 * 2 * es : 0;
     long pc = long((size_t(4) << 30) / (per_item_y + per_item_yh));
     l.pc = pc < 1 ? 1 : (pc > l.bc ? l.bc : pc);
-    if (!use_fused_adjoint(p)) {
+    if (t64) {
+      if (l.pc > kTermItems) l.pc = kTermItems;
+    } else if (!use_fused_adjoint(p)) {
       // sub-chunks that fill the accumulation kernel's resident workgroups in
       // whole rounds, and chunks of whole sub-chunks (no small tail launch per
       // chunk); the chunking does not change any item's result
@@ -1328,6 +1351,7 @@ Layout make_layout(const Plan &p, int64_t batch, int op, long chunk, size_t ws_b
     l.off_dp = o; o += al(size_t(l.bc) * kDomSeg * p.N_rho * sizeof(double));
     l.off_pd = o; o += use_fused_adjoint(p) ? 0 : al(size_t(l.bc) * p.N_rho * p.N * p.N * sizeof(double));
     l.off_yh = o; o += al(size_t(l.pc) * per_item_yh);
+    l.off_zp = o; o += t64 ? al(size_t(kAccParts) * l.bc * n3 * 2 * sizeof(double)) : 0;
     l.total = o;
     return l;
   }
@@ -1346,6 +1370,14 @@ Layout make_layout(const Plan &p, int64_t batch, int op, long chunk, size_t ws_b
     l.pc = pc < 8 ? 8 : (pc > 128 ? 128 : pc);
   }
   if (l.pc > l.bc * p.N_rho) l.pc = l.bc * p.N_rho;
+  const bool t64 = use_vss_terms64(p) && !bil;
+  const size_t per_item_y = size_t(p.N_rho) * ((p.M + 1) / 2) * n3 * 2 * es;
+  if (t64) {
+    // items per launch of the on-chip term loop: their volumes within 2 GiB
+    const long pc = long((size_t(2) << 30) / per_item_y);
+    l.pc = pc < 1 ? 1 : (pc > kTermItems ? kTermItems : pc);
+    if (l.pc > l.bc) l.pc = l.bc;
+  }
   l.off_h = o; o += al(size_t(l.bc) * n3 * 2 * es);
   l.off_h64 = l.off_h;
   if (p.precision == QCOLL_FP32) { l.off_h64 = o; o += al(size_t(l.bc) * n3 * 2 * sizeof(double)); }
@@ -1355,16 +1387,18 @@ Layout make_layout(const Plan &p, int64_t batch, int op, long chunk, size_t ws_b
   const bool half = fused || vss;
   // literal: complex accumulators and one complex low-rank row per kept term
   const size_t per_node = half ? size_t(p.N / 2 + 1) * p.N * p.N * 2 : size_t(n3) * (lit ? 2 : 1);
-  l.off_a = o; o += al(size_t(l.bc) * p.N_rho * per_node * es);
+  l.off_a = o; o += t64 ? 0 : al(size_t(l.bc) * p.N_rho * per_node * es);
   l.off_b = o; o += (p.mix_identity || half) ? 0 : al(size_t(l.bc) * p.nv * n3 * es * (lit ? 2 : 1));
   l.off_w = o; o += half ? 0 : al(size_t(l.bc) * (lit ? p.nv : p.npair()) * n3 * 2 * sizeof(double));
   l.off_t = o; o += al(size_t(l.bc) * n3 * 2 * sizeof(double));   // gain spectrum, FP64
   l.off_l = o; o += al(size_t(l.bc) * n3 * 2 * sizeof(double));
   const bool q64 = use_gain_q64(p) && !bil;   // FP64 gain on chip: no per-term volumes
-  l.off_y = o; o += (fused || q64) ? 0 : al(size_t(l.pc) * p.M * n3 * 2 * es);
+  l.off_y = o;
+  o += (fused || q64) ? 0 : (t64 ? al(size_t(l.pc) * per_item_y) : al(size_t(l.pc) * p.M * n3 * 2 * es));
+  l.off_zp = o; o += t64 ? al(size_t(kAccParts) * l.bc * n3 * 2 * sizeof(double)) : 0;
   // two-pass VSS: the partial half spectra of the accumulation's parts 1.. of a launch
   l.off_vp = o;
-  o += (vss && !fused) ? al(size_t(kVssParts - 1) * l.pc * (p.N / 2 + 1) * p.N * p.N * 2 * es) : 0;
+  o += (vss && !fused && !t64) ? al(size_t(kVssParts - 1) * l.pc * (p.N / 2 + 1) * p.N * p.N * 2 * es) : 0;
   if (lit) {
     l.off_yg = o; o += al(size_t(l.pc) * p.M * n3 * 2 * es);   // the Im(beta) volumes
   }

@@ -1,0 +1,301 @@
+// FP64 term loops that need the spectrum of every term's product, at N = 32:
+// the gain adjoint of the VJP (VHS kernels) and the gain of VSS kernels.
+//
+// k_terms_c2 takes a term on chip to velocity space (c2_inverse: one workgroup
+// per (item, node) pair and class of j1), forms the product there,
+//   adjoint  y = w_q h_p conj(u)             (one volume per term),
+//   VSS      t_q + i t_q', t = Re(u)^2 - Im(u)^2 = t1 t2   (two terms a volume),
+// transforms it forward along axes 3 and 2 on chip and writes the class's
+// planes: 16 bytes a point and volume, written once, where the two-pass
+// schedule writes and reads a term's volume twice (and VSS kernels take a
+// volume per term).  k_acc_terms reads each volume once, transforms it along
+// axis 1 and adds it, weighted, to the item's spectrum
+//   adjoint  Z = sum c_s(k) P(k)                  (2 Re ifft3[Z] is used),
+//   VSS      Z = sum (alpha_q - i alpha_q')(k) P(k)     (Re ifft3[Z]: alpha is
+//            even and real, so C_q t_q + C_q' t_q' is the real part).
+// k_terms_c2 is bound like k_gain_c2 (VALU issue, LDS and L2 reads in turn)
+// with half of its transforms more, k_acc_terms by its reads.
+#include <hip/hip_runtime.h>
+
+#include "qcoll_c2.hpp"
+
+namespace qcoll {
+
+// MODE 0: adjoint, volumes (pair, q); MODE 1: VSS, volumes (pair, q / 2).
+// H: spectra of the items, pairs [bp0, bp0 + nbp) of them; Hp: h_p of every pair
+// (MODE 0); Y: volumes [j1][k2][k3] from pair bp0 on; dots: [2 pairs] parts of
+// <h_p, A_p> by class, or null.
+template <int N, int MODE>
+__global__ __launch_bounds__(C2Geom<N>::NL) void k_terms_c2(const cplx<double> *__restrict__ H,
+                                                           const cplx<double> *__restrict__ phase,
+                                                           const double *__restrict__ wq,
+                                                           const double *__restrict__ Hp,
+                                                           cplx<double> *__restrict__ Y, double *__restrict__ dots,
+                                                           long bp0, long nbp, int M, int Nr, double scale) {
+  using Gm = C2Geom<N>;
+  constexpr int NV = Gm::NV, R = Gm::R, S = Gm::S;
+  constexpr long n2 = long(N) * N, n3 = n2 * N;
+  extern __shared__ double tile[];
+
+  const long lb = xcd_block();
+  if (lb >= nbp * 2) return;  // uniform per workgroup
+  const long bpl = lb / 2, bp = bp0 + bpl;
+  const int g = int(lb % 2);
+  const long b = bp / Nr;
+  const int p = int(bp % Nr);
+  const int lane = threadIdx.x;
+  const int vb = lane / N, cb = lane % N;   // plane v and row j2 (k3 after the transpose back)
+  const __amdgpu_buffer_rsrc_t hr = make_rsrc(H + b * n3, unsigned(n3 * sizeof(cplx<double>)));
+  cplx<double> *b1s = reinterpret_cast<cplx<double> *>(tile + NV * S);
+  if (lane < N) b1s[lane] = phase[size_t(p * M) * 3 * N + lane];
+  __syncthreads();
+
+  const int MV = MODE == 0 ? M : (M + 1) / 2;   // volumes of a pair
+  double keep[N];   // MODE 0: the lane's row of h_p; MODE 1: the product of the volume's first term
+  if constexpr (MODE == 0) {
+    const double2 *h = reinterpret_cast<const double2 *>(Hp + bp * n3 + long(2 * vb + g) * n2 + long(cb) * N);
+    static_for<0, N / 2>([&](auto j) {
+      const double2 v = h[decltype(j)::value];
+      keep[2 * decltype(j)::value] = v.x;
+      keep[2 * decltype(j)::value + 1] = v.y;
+    });
+  }
+  double dot = 0.0;
+  const int yo = (int(2 * vb + g) * int(n2) + cb) * int(sizeof(cplx<double>));
+  auto inverse = [&](int q, double sc, double *zr, double *zi) {
+    const cplx<double> *ph = phase + size_t(p * M + q) * 3 * N;
+    cplx<double> b1n{};
+    if (lane < N && q + 1 < M) b1n = ph[3 * N + lane];
+    c2_inverse<N>(tile, hr, ph, b1s + (q & 1) * N, g, lane, sc, [&]() {
+      if (lane < N && q + 1 < M) b1s[((q + 1) & 1) * N + lane] = b1n;
+    }, zr, zi);
+  };
+  for (int vol = 0; vol < MV; ++vol) {
+    double zr[N], zi[N];
+    if constexpr (MODE == 0) {
+      // u carries sqrt(w_q): y = w_q h conj(u) and w_q h (Re(u)^2 - Im(u)^2)
+      const double sw = __builtin_sqrt(wq[vol]);
+      inverse(vol, scale * sw, zr, zi);
+      double part = 0.0;
+      static_for<0, N>([&](auto j) {
+        constexpr int jj = decltype(j)::value;
+        part += keep[jj] * (zr[jj] * zr[jj] - zi[jj] * zi[jj]);
+        const double s = sw * keep[jj];
+        zr[jj] = s * zr[jj];
+        zi[jj] = -s * zi[jj];
+      });
+      dot += part;
+    } else {
+      inverse(2 * vol, scale, zr, zi);
+      static_for<0, N>([&](auto j) {
+        constexpr int jj = decltype(j)::value;
+        keep[jj] = zr[jj] * zr[jj] - zi[jj] * zi[jj];
+        zi[jj] = 0.0;   // an odd last term stands alone
+      });
+      if (2 * vol + 1 < M) {
+        inverse(2 * vol + 1, scale, zr, zi);
+        static_for<0, N>([&](auto j) {
+          constexpr int jj = decltype(j)::value;
+          zi[jj] = zr[jj] * zr[jj] - zi[jj] * zi[jj];
+        });
+      }
+      static_for<0, N>([&](auto j) { zr[decltype(j)::value] = keep[decltype(j)::value]; });
+    }
+    fft_reg<N, -1, double>(zr, zi);   // axis 3: lane (v, j2) holds k3
+    // C -> B inside the wave's own planes: element (v, j2, k3) at v*S + j2*R + k3
+    auto c_to_b = [&](double *z) {
+      static_for<0, N>([&](auto kk) { tile[vb * S + cb * R + decltype(kk)::value] = z[decltype(kk)::value]; });
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      static_for<0, N>([&](auto jj) { z[decltype(jj)::value] = tile[vb * S + decltype(jj)::value * R + cb]; });
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    c_to_b(zr);
+    c_to_b(zi);
+    fft_reg<N, -1, double>(zr, zi);   // axis 2: lane (v, k3) holds k2
+    const __amdgpu_buffer_rsrc_t yr = make_rsrc(Y + (bpl * MV + vol) * n3, unsigned(n3 * sizeof(cplx<double>)));
+    static_for<0, N>([&](auto kk) {
+      typedef unsigned u4v __attribute__((ext_vector_type(4)));
+      __builtin_amdgcn_raw_buffer_store_b128(
+          __builtin_bit_cast(u4v, double2{zr[decltype(kk)::value], zi[decltype(kk)::value]}), yr, yo,
+          int(decltype(kk)::value * N * sizeof(cplx<double>)), 0);
+    });
+  }
+  if constexpr (MODE == 0) {
+    if (dots) {
+      // the lanes' parts in a fixed order: wave butterflies, then the waves
+      double *red = tile;
+      __syncthreads();
+      for (int o = 32; o > 0; o >>= 1) dot += __shfl_xor(dot, o);
+      if (lane % 64 == 0) red[lane / 64] = dot;
+      __syncthreads();
+      if (lane == 0) {
+        double s = 0.0;
+        for (int w = 0; w < Gm::NL / 64; ++w) s += red[w];
+        dots[bp * 2 + g] = s;
+      }
+    }
+  }
+}
+
+// Z part: one lane per pencil (k2, k3) of an item and per parity G of k1 (the
+// transform's other outputs are dropped at compile time, which leaves room for
+// the sums beside the pencil), over the volumes of the nodes
+// [part Nr / kAccParts, (part + 1) Nr / kAccParts): a fixed split, so that an
+// item's result does not depend on the launch.
+template <int N, int MODE, int G>
+__device__ __forceinline__ void acc_terms(const cplx<double> *__restrict__ Y, const cplx<double> *__restrict__ phase,
+                                          const double *__restrict__ apq, cplx<double> *__restrict__ Z, long bl,
+                                          int pen, int p0, int p1, int M, int Nr) {
+  constexpr int n2 = N * N, HN = N / 2;
+  constexpr long n3 = long(n2) * N, nh = long(HN + 1) * n2;
+  const int MV = MODE == 0 ? M : (M + 1) / 2;
+  const int k2 = pen / N, k3 = pen % N;
+  const int refl = ((N - k2) % N) * N + (N - k3) % N;
+  double ar[HN], ai[HN];
+  static_for<0, HN>([&](auto i) { ar[decltype(i)::value] = 0.0; ai[decltype(i)::value] = 0.0; });
+  // k1 of sum i: the outputs of column k = G mod 2 of the decimated transform
+  constexpr auto k1_of = [](int i) { return G + 2 * (i / 4) + (N / 4) * (i % 4); };
+  for (int p = p0; p < p1; ++p) {
+    for (int v = 0; v < MV; ++v) {
+      const __amdgpu_buffer_rsrc_t yr =
+          make_rsrc(Y + ((bl * Nr + p) * MV + v) * n3, unsigned(n3 * sizeof(cplx<double>)));
+      double xr[N], xi[N];
+      static_for<0, N>([&](auto j) {
+        const cplx<double> x = load_c64(yr, pen * int(sizeof(cplx<double>)),
+                                        int(decltype(j)::value * n2 * sizeof(cplx<double>)));
+        xr[decltype(j)::value] = x.re;
+        xi[decltype(j)::value] = x.im;
+      });
+      if constexpr (MODE == 0) {
+        const cplx<double> *ph = phase + size_t(p * M + v) * 3 * N;
+        const cplx<double> b2 = ph[N + k2], b3 = ph[2 * N + k3];
+        const double x = b2.re * b3.re - b2.im * b3.im, y = b2.re * b3.im + b2.im * b3.re;
+        const double P = x + y, Q = x - y;
+        fft_reg<N, -1, double>(xr, xi);
+        static_for<0, HN>([&](auto i) {
+          constexpr int ii = decltype(i)::value, k1 = k1_of(ii);
+          const cplx<double> b1 = ph[k1];
+          const double c = b1.re * P + b1.im * Q;
+          ar[ii] += c * xr[k1];
+          ai[ii] += c * xi[k1];
+        });
+      } else {
+        // alpha_pq on the planes k1 <= N/2; plane k1 > N/2 at the reflected index
+        const double *a0 = apq + (size_t(p) * M + 2 * v) * nh;
+        const bool two = 2 * v + 1 < M;
+        const double *a1 = two ? a0 + nh : a0;
+        fft_reg<N, -1, double>(xr, xi);
+        static_for<0, HN>([&](auto i) {
+          constexpr int ii = decltype(i)::value, k1 = k1_of(ii);
+          const int o = k1 <= HN ? k1 * n2 + pen : (N - k1) * n2 + refl;
+          const double w0 = a0[o], r1 = a1[o], w1 = two ? r1 : 0.0;
+          // (w0 - i w1)(x + i y)
+          ar[ii] += w0 * xr[k1] + w1 * xi[k1];
+          ai[ii] += w0 * xi[k1] - w1 * xr[k1];
+        });
+      }
+    }
+  }
+  cplx<double> *z = Z + bl * n3 + pen;
+  static_for<0, HN>([&](auto i) {
+    z[k1_of(decltype(i)::value) * n2] = cplx<double>{ar[decltype(i)::value], ai[decltype(i)::value]};
+  });
+}
+
+template <int N, int MODE>
+__global__ __launch_bounds__(256, 2) void k_acc_terms(const cplx<double> *__restrict__ Y,
+                                                      const cplx<double> *__restrict__ phase,
+                                                      const double *__restrict__ apq, cplx<double> *__restrict__ Z,
+                                                      long part_stride, int M, int Nr) {
+  // a workgroup: 128 pencils, waves 0 and 1 their even k1, waves 2 and 3 the odd
+  constexpr int GP = N * N / 128;
+  const long bl = blockIdx.x / GP;
+  const int wave = int(threadIdx.x) / 64;
+  const int pen = int(blockIdx.x % GP) * 128 + (wave % 2) * 64 + int(threadIdx.x) % 64;
+  const int part = int(blockIdx.y);
+  const int p0 = part * Nr / kAccParts, p1 = (part + 1) * Nr / kAccParts;
+  cplx<double> *z = Z + part * part_stride;
+  if (wave < 2) acc_terms<N, MODE, 0>(Y, phase, apq, z, bl, pen, p0, p1, M, Nr);
+  else acc_terms<N, MODE, 1>(Y, phase, apq, z, bl, pen, p0, p1, M, Nr);
+}
+
+// dwg[pair] = both classes' parts
+__global__ __launch_bounds__(256) void k_class_dots(const double *dots, double *dwg, long n) {
+  const long i = long(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (i < n) dwg[i] = dots[2 * i] + dots[2 * i + 1];
+}
+
+static bool terms64_supported(const Plan &p) { return p.precision == QCOLL_FP64 && p.N == 32 && !p.literal; }
+
+bool use_adjoint_terms64(const Plan &p) { return terms64_supported(p) && p.schedule_user != 1 && !p.is_vss(); }
+
+bool use_vss_terms64(const Plan &p) { return terms64_supported(p) && p.schedule != 1 && p.is_vss(); }
+
+template <int MODE>
+static qcoll_status launch_terms64(const Plan &p, const cplx<double> *H, const double *Hp, cplx<double> *Y,
+                                   cplx<double> *Z, long part_stride, double *dots, long it0, long ni,
+                                   hipStream_t st) {
+  constexpr int N = 32;
+  using G = C2Geom<N>;
+  if (hipFuncSetAttribute(reinterpret_cast<const void *>(&k_terms_c2<N, MODE>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, int(G::lds_bytes)) != hipSuccess) {
+    set_error("hipFuncSetAttribute failed for the FP64 term kernel");
+    return QCOLL_EDEVICE;
+  }
+  const auto *ph = reinterpret_cast<const cplx<double> *>(p.phase);
+  const long nbp = ni * p.N_rho;
+  {
+    TimedLaunch tl(MODE == 0 ? "vjp terms c2" : "vss terms c2", st);
+    hipLaunchKernelGGL((k_terms_c2<N, MODE>), dim3(unsigned(nbp * 2)), dim3(G::NL), G::lds_bytes, st, H, ph,
+                       reinterpret_cast<const double *>(p.wq), Hp, Y, dots, it0 * p.N_rho, nbp, p.M, p.N_rho,
+                       1.0 / double(long(N) * N * N));
+  }
+  {
+    TimedLaunch tl(MODE == 0 ? "vjp terms acc" : "vss terms acc", st);
+    hipLaunchKernelGGL((k_acc_terms<N, MODE>), dim3(unsigned(ni * (N * N / 128)), kAccParts), dim3(256), 0, st, Y, ph,
+                       static_cast<const double *>(p.alpha_pq), Z + it0 * long(N) * N * N, part_stride, p.M,
+                       p.N_rho);
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) {
+    set_error(std::string("FP64 terms: ") + hipGetErrorString(e));
+    return QCOLL_EDEVICE;
+  }
+  return QCOLL_OK;
+}
+
+qcoll_status launch_adjoint_terms64(const Plan &p, const void *H, const double *Hp, void *Y, void *Z,
+                                    long part_stride, double *dots, double *dwg, long nb, long pc, hipStream_t st) {
+  for (long i0 = 0; i0 < nb; i0 += pc) {
+    const qcoll_status s = launch_terms64<0>(p, static_cast<const cplx<double> *>(H), Hp,
+                                             static_cast<cplx<double> *>(Y), static_cast<cplx<double> *>(Z),
+                                             part_stride, dots, i0, nb - i0 < pc ? nb - i0 : pc, st);
+    if (s != QCOLL_OK) return s;
+  }
+  if (dots) {
+    const long n = nb * p.N_rho;
+    hipLaunchKernelGGL(k_class_dots, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st, dots, dwg, n);
+    if (hipGetLastError() != hipSuccess) {
+      set_error("FP64 terms: class dots launch failed");
+      return QCOLL_EDEVICE;
+    }
+  }
+  return QCOLL_OK;
+}
+
+qcoll_status launch_vss_terms64(const Plan &p, const void *H, void *Y, void *Z, long part_stride, long nb, long pc,
+                                hipStream_t st) {
+  for (long i0 = 0; i0 < nb; i0 += pc) {
+    const qcoll_status s = launch_terms64<1>(p, static_cast<const cplx<double> *>(H), nullptr,
+                                             static_cast<cplx<double> *>(Y), static_cast<cplx<double> *>(Z),
+                                             part_stride, nullptr, i0, nb - i0 < pc ? nb - i0 : pc, st);
+    if (s != QCOLL_OK) return s;
+  }
+  return QCOLL_OK;
+}
+
+}  // namespace qcoll

@@ -362,4 +362,22 @@ struct DstCplxHalf {
   __device__ void operator()(long g, int r, int c, C<T> v) const { out[(half_slab<N>(g) * N + r) * N + c] = v; }
 };
 
+// the sum of kAccParts volumes part_stride elements apart, in order
+template <typename T, int N>
+struct SrcParts {
+  const C<T> *in;
+  long part_stride;
+  __device__ C<T> operator()(long g, int r, int c) const {
+    const C<T> *x = in + (g * N + r) * N + c;
+    C<T> a = x[0];
+#pragma unroll
+    for (int k = 1; k < kAccParts; ++k) {
+      const C<T> b = x[k * part_stride];
+      a.re += b.re;
+      a.im += b.im;
+    }
+    return a;
+  }
+};
+
 }  // namespace qcoll

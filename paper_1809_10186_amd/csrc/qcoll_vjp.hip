@@ -13,7 +13,9 @@
 //
 // The gain adjoint runs on chip per (item, p) pair for FP32 plans with N <= 32
 // (k_adj_fused, qcoll_adj_fused.hip).  Otherwise (FP64, N = 48, or the two-pass
-// schedule requested) it takes three passes per (item, p, q): the forward slab
+// schedule requested) FP64 at N = 32 (VHS kernels) takes the terms to their
+// products' spectra along axes 2 and 3 on chip and sums them in one pass
+// (qcoll_pair64.hip); the rest takes three passes per (item, p, q): the forward slab
 // pass of the hot loop, a pencil pass that inverts along axis 1, forms
 // w_q h_p conj(u), accumulates <h_p, A_p> and transforms back along axis 1, and
 // a slab pass that transforms the two inner axes forward and accumulates
@@ -659,6 +661,8 @@ struct Vjp {
     const bool vss = p.is_vss();
     const int S = p.nv, np = p.npair(), Nr = p.N_rho, M = p.M;
     const bool fused_adjoint = std::is_same<T, float>::value && use_fused_adjoint(p);
+    const bool terms64 = use_adjoint_terms64(p);
+    C<T> *Zp = reinterpret_cast<C<T> *>(w + lay.off_zp);
     qcoll_status s;
     for (long b0 = 0; b0 < batch; b0 += lay.bc) {
       const long nb = (batch - b0 < lay.bc) ? (batch - b0) : lay.bc;
@@ -708,6 +712,15 @@ struct Vjp {
         if ((s = P::template slab<SrcCplxHalf<T, N>, DstCplxHalf<T, N>, +1>(
                  SrcCplxHalf<T, N>{Z}, DstCplxHalf<T, N>{Z}, nb * H1, st, "vjp inverse slab")))
           return s;
+      } else if (terms64) {
+        if constexpr (std::is_same<T, double>::value && N == 32) {
+          const long stride = lay.bc * n3;
+          if ((s = launch_adjoint_terms64(p, H64, Hp, Y, Zp, stride, domega ? pdots : nullptr, dwg, nb, lay.pc, st)))
+            return s;
+          if ((s = P::template slab<SrcParts<T, N>, DstCplx<T, N>, +1>(SrcParts<T, N>{Zp, stride}, DstCplx<T, N>{Z},
+                                                                        nb * N, st, "vjp inverse slab")))
+            return s;
+        }
       } else {
         // gain adjoint, items in sub-chunks of lay.pc items
         const T scale = T(1.0 / double(n3));
