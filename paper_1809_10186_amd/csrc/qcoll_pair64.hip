@@ -51,7 +51,7 @@ __global__ __launch_bounds__(C2Geom<N>::NL) void k_terms_c2(const cplx<double> *
   __syncthreads();
 
   const int MV = MODE == 0 ? M : (M + 1) / 2;   // volumes of a pair
-  double keep[N];   // MODE 0: the lane's row of h_p; MODE 1: the product of the volume's first term
+  double keep[MODE == 0 ? N : 1];   // the lane's row of h_p
   if constexpr (MODE == 0) {
     const double2 *h = reinterpret_cast<const double2 *>(Hp + bp * n3 + long(2 * vb + g) * n2 + long(cb) * N);
     static_for<0, N / 2>([&](auto j) {
@@ -70,7 +70,11 @@ __global__ __launch_bounds__(C2Geom<N>::NL) void k_terms_c2(const cplx<double> *
       if (lane < N && q + 1 < M) b1s[((q + 1) & 1) * N + lane] = b1n;
     }, zr, zi);
   };
+  // scratch in a volume: the lane's plane j1 = 2v + g as [j][j2] doubles, which
+  // only its own wave writes
+  const int ko = int(2 * vb + g) * int(n2 * sizeof(cplx<double>)) + cb * int(sizeof(double));
   for (int vol = 0; vol < MV; ++vol) {
+    const __amdgpu_buffer_rsrc_t yr = make_rsrc(Y + (bpl * MV + vol) * n3, unsigned(n3 * sizeof(cplx<double>)));
     double zr[N], zi[N];
     if constexpr (MODE == 0) {
       // u carries sqrt(w_q): y = w_q h conj(u) and w_q h (Re(u)^2 - Im(u)^2)
@@ -86,20 +90,31 @@ __global__ __launch_bounds__(C2Geom<N>::NL) void k_terms_c2(const cplx<double> *
       });
       dot += part;
     } else {
-      inverse(2 * vol, scale, zr, zi);
-      static_for<0, N>([&](auto j) {
-        constexpr int jj = decltype(j)::value;
-        keep[jj] = zr[jj] * zr[jj] - zi[jj] * zi[jj];
-        zi[jj] = 0.0;   // an odd last term stands alone
-      });
-      if (2 * vol + 1 < M) {
-        inverse(2 * vol + 1, scale, zr, zi);
+      for (int q = 2 * vol; q < M && q < 2 * vol + 2; ++q) {
+        inverse(q, scale, zr, zi);
         static_for<0, N>([&](auto j) {
           constexpr int jj = decltype(j)::value;
-          zi[jj] = zr[jj] * zr[jj] - zi[jj] * zi[jj];
+          zr[jj] = zr[jj] * zr[jj] - zi[jj] * zi[jj];
         });
+        if ((q & 1) == 0 && q + 1 < M) {
+          // the first product waits in the volume's own place (this lane's
+          // values, read back below): held in registers it spills as much
+          static_for<0, N>([&](auto j) {
+            typedef unsigned u2v __attribute__((ext_vector_type(2)));
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2v, zr[decltype(j)::value]), yr, ko,
+                                                  int(decltype(j)::value * N * sizeof(double)), 0);
+          });
+        }
       }
-      static_for<0, N>([&](auto j) { zr[decltype(j)::value] = keep[decltype(j)::value]; });
+      const bool two = 2 * vol + 1 < M;
+      static_for<0, N>([&](auto j) {
+        constexpr int jj = decltype(j)::value;
+        double first = 0.0;
+        if (two)
+          first = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(yr, ko, int(jj * N * sizeof(double)), 0));
+        zi[jj] = two ? zr[jj] : 0.0;
+        zr[jj] = two ? first : zr[jj];
+      });
     }
     fft_reg<N, -1, double>(zr, zi);   // axis 3: lane (v, j2) holds k3
     // C -> B inside the wave's own planes: element (v, j2, k3) at v*S + j2*R + k3
@@ -116,12 +131,12 @@ __global__ __launch_bounds__(C2Geom<N>::NL) void k_terms_c2(const cplx<double> *
     c_to_b(zr);
     c_to_b(zi);
     fft_reg<N, -1, double>(zr, zi);   // axis 2: lane (v, k3) holds k2
-    const __amdgpu_buffer_rsrc_t yr = make_rsrc(Y + (bpl * MV + vol) * n3, unsigned(n3 * sizeof(cplx<double>)));
+    // streaming stores (nt): read once, by k_acc_terms
     static_for<0, N>([&](auto kk) {
       typedef unsigned u4v __attribute__((ext_vector_type(4)));
       __builtin_amdgcn_raw_buffer_store_b128(
           __builtin_bit_cast(u4v, double2{zr[decltype(kk)::value], zi[decltype(kk)::value]}), yr, yo,
-          int(decltype(kk)::value * N * sizeof(cplx<double>)), 0);
+          int(decltype(kk)::value * N * sizeof(cplx<double>)), 2);
     });
   }
   if constexpr (MODE == 0) {
@@ -161,6 +176,7 @@ __device__ __forceinline__ void acc_terms(const cplx<double> *__restrict__ Y, co
   constexpr auto k1_of = [](int i) { return G + 2 * (i / 4) + (N / 4) * (i % 4); };
   for (int p = p0; p < p1; ++p) {
     for (int v = 0; v < MV; ++v) {
+      __syncthreads();   // both parities read a volume together (the second from cache)
       const __amdgpu_buffer_rsrc_t yr =
           make_rsrc(Y + ((bl * Nr + p) * MV + v) * n3, unsigned(n3 * sizeof(cplx<double>)));
       double xr[N], xi[N];
