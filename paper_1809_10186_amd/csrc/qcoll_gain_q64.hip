@@ -341,6 +341,8 @@ static qcoll_status launch_onchip64(const Plan &p, Kern kern, int lanes, size_t 
 bool gain_q64_supported(int N, int precision) { return precision == QCOLL_FP64 && (N == 16 || N == 32); }
 
 bool use_gain_q64(const Plan &p) {
+  // at N = 24 the on-chip loop is the automatic choice, not one to request
+  if (p.N == 24) return p.schedule == 0 && p.precision == QCOLL_FP64 && !p.is_vss() && !p.literal;
   return p.schedule != 1 && !p.is_vss() && !p.literal && gain_q64_supported(p.N, p.precision);
 }
 
@@ -353,6 +355,7 @@ qcoll_status launch_gain_q64(const Plan &p, const void *H, double *A, void *U, l
     case 16:
       return launch_onchip64<16, 4, 0>(p, u ? &k_gain_q64<16, true> : &k_gain_q64<16, false>, G16::NL,
                                        G16::lds_bytes, "gain q64", h, A, u, nbp, st);
+    case 24: return launch_gain_cls24(p, h, A, nbp, st);   // never split by terms
     case 32:
       return launch_onchip64<32, 2, 32>(p, u ? &k_gain_c2<32, true> : &k_gain_c2<32, false>, G32::NL,
                                         G32::lds_bytes, "gain c2", h, A, u, nbp, st);

@@ -277,13 +277,22 @@ static std::vector<int> tune_chunks(int64_t batch) {
   return out;
 }
 
+// The on-chip candidate of the autotuner: schedule 2, or 0 where the on-chip loop
+// is the automatic choice but not one to request (FP64 at N = 24); -1: none.
+static int onchip_candidate(const qcoll::Plan &p) {
+  if (qcoll::onchip_schedule_supported(p)) return 2;
+  qcoll::Plan a = p;
+  a.schedule = 0;
+  return qcoll::use_gain_q64(a) ? 0 : -1;
+}
+
 // the largest candidate layout, with optional parts as far as ws_bytes holds them
 static size_t autotune_bytes(qcoll_plan plan, int64_t batch, size_t ws_bytes) {
   qcoll::Plan p = plan->p;  // copy: only schedule/chunk are varied
   size_t mx = 0;
-  for (int sch : {1, 2})
+  for (int sch : {1, onchip_candidate(p)})
     for (int ck : tune_chunks(batch)) {
-      if (sch == 2 && !qcoll::onchip_schedule_supported(p)) continue;
+      if (sch < 0) continue;
       p.schedule = sch;
       p.chunk = ck;
       mx = std::max(mx, qcoll::make_layout(p, batch, 0, 0, ws_bytes).total);
@@ -299,14 +308,17 @@ size_t qcoll_autotune_workspace_bytes(qcoll_plan plan, int64_t batch) {
 // Cache entries carry the schedule set they were timed against ("s2": the FP32
 // fused kernels, the FP64 on-chip kernels at 16^3 and 32^3); a build that adds
 // or changes a schedule bumps it, so that an older entry is timed again
-// instead of pinning a plan to what used to be the faster schedule.
-constexpr int kTuneScheduleSet = 2;
+// instead of pinning a plan to what used to be the faster schedule ("s3": the
+// FP64 on-chip loops at 24^3 and, for VSS kernels, at 32^3).
+static int tune_schedule_set(const qcoll::Plan &p) {
+  return p.precision == QCOLL_FP64 && (p.N == 24 || (p.N == 32 && p.is_vss())) ? 3 : 2;
+}
 
 static std::string tune_key(const qcoll::Plan &p, int64_t batch) {
   int bucket = 1;
   while (bucket < batch && bucket < (1 << 20)) bucket <<= 1;
   std::ostringstream k;
-  k << "gfx950 s" << kTuneScheduleSet << " N=" << p.N << " Nr=" << p.N_rho << " M=" << p.M
+  k << "gfx950 s" << tune_schedule_set(p) << " N=" << p.N << " Nr=" << p.N_rho << " M=" << p.M
     << " prec=" << p.precision << " rank=" << p.rank << " batch<=" << bucket;
   return k.str();
 }
@@ -325,17 +337,17 @@ qcoll_status qcoll_autotune(qcoll_plan plan, int64_t batch, const double *f, dou
     while (std::getline(in, line)) {
       const size_t bar = line.find('|');
       if (bar == std::string::npos || line.substr(0, bar) != key) continue;
-      // "<schedule> <chunk> [ms]": schedule 1 or 2, chunk 1..65536; anything
+      // "<schedule> <chunk> [ms]": a candidate schedule, chunk 1..65536; anything
       // else (garbage, out-of-range numbers) is skipped
       const char *c0 = line.c_str() + bar + 1;
       char *e1 = nullptr, *e2 = nullptr;
       errno = 0;
       const long sch_l = std::strtol(c0, &e1, 10);
       const long ck_l = (e1 != c0) ? std::strtol(e1, &e2, 10) : 0;
-      const bool parsed = errno == 0 && e1 != c0 && e2 && e2 != e1 && (sch_l == 1 || sch_l == 2) && ck_l >= 1 &&
+      const bool parsed = errno == 0 && e1 != c0 && e2 && e2 != e1 && (sch_l == 1 || sch_l == onchip_candidate(p)) && ck_l >= 1 &&
                           ck_l <= 65536;
       const int sch = int(sch_l), ck = int(ck_l);
-      if (parsed && (sch != 2 || qcoll::onchip_schedule_supported(p))) {
+      if (parsed) {
         p.schedule = sch;
         p.chunk = ck;
         ++p.gen;
@@ -355,9 +367,9 @@ qcoll_status qcoll_autotune(qcoll_plan plan, int64_t batch, const double *f, dou
   const bool timing = qcoll::timing_on();
   qcoll_timing_enable(0);
   qcoll_status rc = QCOLL_OK;
-  for (int sch : {2, 1})
+  for (int sch : {onchip_candidate(p), 1})
     for (int ck : tune_chunks(batch)) {
-      if (sch == 2 && !qcoll::onchip_schedule_supported(p)) continue;
+      if (sch < 0) continue;
       p.schedule = sch;
       p.chunk = ck;
       const qcoll::Layout lay = qcoll::make_layout(p, batch, 0, 0, ws_bytes);

@@ -1284,7 +1284,10 @@ bool split_terms(const Plan &p, long nbp) {
   switch (p.N) {
     case 12: t = 2.0; slots = 1024; break;
     case 16: t = dp ? 6.5 : 2.5; slots = dp ? 2048 : 1024; wgs = dp ? 4.0 : 1.0; break;
-    case 24: t = 7.5; slots = 512; break;
+    case 24:
+      if (dp) return false;
+      t = 7.5; slots = 512;
+      break;
     case 32: t = dp ? 12.0 : 9.5; slots = 256; wgs = dp ? 2.0 : 1.0; break;
     default: return false;
   }
