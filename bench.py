@@ -161,8 +161,8 @@ def algorithmic_bytes(role, fp32, B, N, Nr, M, npair, nv, half=None):
         # complex FP64 volumes out; then the pencil sum over the pairs
         "low-rank slab": B * npair * n3 * (2 * es + c64),
         "low-rank pencil": B * n3 * (npair * c64 + c64),
-        "gain inverse slab": B * (nh if half else n3) * (c64 + c64),
-        "loss slab": B * (nh if half else n3) * (16 + 16),
+        # gain and loss in one launch
+        "inverse slabs": B * (nh if half else n3) * (c64 + c64 + 16 + 16),
         # gain and loss spectra in (complex FP64), f in and Q out (FP64)
         "assemble": B * ((nh * (c64 + 16) + n3 * 16) if half else n3 * (c64 + 16 + 16)),
         # Nr FP32 half spectra in, one FP64 half spectrum out

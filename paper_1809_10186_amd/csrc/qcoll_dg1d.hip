@@ -17,6 +17,7 @@
 #include <cmath>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "qcoll_internal.h"
@@ -25,6 +26,7 @@ namespace qcoll {
 namespace {
 
 constexpr int kMaxK = 8;
+constexpr int kWallSeg = 8;   // workgroups per wall (one each took 10 us of loads in sequence)
 
 // per-end data of the boundary kernels
 struct EndDev {
@@ -37,12 +39,14 @@ struct EndDev {
 
 struct Dg1dArgs {
   const double *F;
-  double *R;
+  double *R;            // cz L(F), plus cx X + cy Y where X is set (an SSP-RK stage)
+  const double *X, *Y;
+  double cx, cy, cz;
   const double *C;      // collision term per node (scaled by cscale), or null
   double cscale;
   const double *J;      // [I]
   const double *tab;    // w[K], S[K][K], phiL[K], phiR[K]
-  double *nw;           // [2] wall densities
+  double *nw;           // [2][kWallSeg] parts of the wall densities
   EndDev end[2];
   int I, K, N;
   long n3;
@@ -50,49 +54,59 @@ struct Dg1dArgs {
   int periodic;
 };
 
-__device__ __forceinline__ double c1_of(long j, int N, double L) {
-  const int j1 = int(j / (long(N) * N));
+__device__ __forceinline__ double c1_of(int j, int N, double L) {
+  const int j1 = j / (N * N);
   return -L + (j1 + 0.5) * (2.0 * L / N);
 }
 
-// wall densities: block 0 left, block 1 right; n_w = -sum_{(c-u).n >= 0} (c-u).n f_trace / den
-__global__ __launch_bounds__(1024) void k_dg1d_wall(Dg1dArgs a) {
-  const int side = blockIdx.x;
+// wall densities, left then right: n_w = -sum_{(c-u).n >= 0} (c-u).n f_trace / den,
+// each in kWallSeg parts that the transport kernel adds in order.  KC: K at
+// compile time (0: at run time).
+template <int KC>
+__global__ __launch_bounds__(256) void k_dg1d_wall(Dg1dArgs a) {
+  const int K = KC > 0 ? KC : a.K;
+  const int side = blockIdx.x / kWallSeg, seg = blockIdx.x % kWallSeg;
   const EndDev &E = a.end[side];
   if (E.kind != QCOLL_BC_WALL) return;   // uniform per block
   const int e = side == 0 ? 0 : a.I - 1;
-  const double *phi = a.tab + a.K + a.K * a.K + (side == 0 ? 0 : a.K);
+  const double *phi = a.tab + K + K * K + (side == 0 ? 0 : K);
+  const double *f = a.F + long(e) * K * a.n3;
+  const int n3 = int(a.n3), len = (n3 + kWallSeg - 1) / kWallSeg;
+  const int j1 = (seg + 1) * len < n3 ? (seg + 1) * len : n3;
   double s = 0.0;
-  for (long j = threadIdx.x; j < a.n3; j += 1024) {
+#pragma unroll 4
+  for (int j = seg * len + int(threadIdx.x); j < j1; j += 256) {
     const double cn = (c1_of(j, a.N, a.L) - E.ux) * E.nrm;
-    if (cn >= 0.0) {
-      double tr = 0.0;
-      for (int l = 0; l < a.K; ++l) tr += phi[l] * a.F[(long(e) * a.K + l) * a.n3 + j];
-      s += cn * tr;
-    }
+    double tr = 0.0;
+    for (int l = 0; l < K; ++l) tr += phi[l] * f[l * a.n3 + j];
+    s += cn >= 0.0 ? cn * tr : 0.0;
   }
-  __shared__ double red[1024];
-  red[threadIdx.x] = s;
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  __shared__ double red[4];
+  if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = s;
   __syncthreads();
-  for (int w = 512; w > 0; w >>= 1) {
-    if (int(threadIdx.x) < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) a.nw[side] = -red[0] / E.den;
+  if (threadIdx.x == 0) a.nw[blockIdx.x] = -(((red[0] + red[1]) + red[2]) + red[3]) / E.den;
 }
 
 // exterior state of an end for velocity point j (incoming side of the face)
-__device__ __forceinline__ double ext_state(const Dg1dArgs &a, int side, long j) {
+__device__ __forceinline__ double ext_state(const Dg1dArgs &a, int side, int j) {
   const EndDev &E = a.end[side];
-  return E.kind == QCOLL_BC_WALL ? a.nw[side] * E.fb[j] : E.fb[j];
+  if (E.kind != QCOLL_BC_WALL) return E.fb[j];
+  double nw = 0.0;
+#pragma unroll
+  for (int k = 0; k < kWallSeg; ++k) nw += a.nw[side * kWallSeg + k];
+  return nw * E.fb[j];
 }
 
-__global__ __launch_bounds__(256) void k_dg1d_rhs(Dg1dArgs a) {
-  const long t = long(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= long(a.I) * a.n3) return;
-  const int e = int(t / a.n3);
-  const long j = t % a.n3;
-  const int K = a.K;
+// R = cz L(F) (+ cx X + cy Y): the stage's update rides on the transport's
+// store, instead of a pass of its own over R and the states
+template <int KC>
+__global__ __launch_bounds__(256) void k_dg1d_rhs(Dg1dArgs a, int nblk) {
+  constexpr int KM = KC > 0 ? KC : kMaxK;
+  const int e = int(blockIdx.x) / nblk;
+  const int j = (int(blockIdx.x) % nblk) * 256 + int(threadIdx.x);
+  if (j >= int(a.n3)) return;
+  const int K = KC > 0 ? KC : a.K;
   const double *w = a.tab, *S = a.tab + K, *phiL = a.tab + K + K * K, *phiR = phiL + K;
   const double cx = c1_of(j, a.N, a.L);
   auto trace = [&](int el, const double *phi) {
@@ -100,7 +114,7 @@ __global__ __launch_bounds__(256) void k_dg1d_rhs(Dg1dArgs a) {
     for (int l = 0; l < K; ++l) s += phi[l] * a.F[(long(el) * K + l) * a.n3 + j];
     return s;
   };
-  double f[kMaxK];
+  double f[KM];
   for (int l = 0; l < K; ++l) f[l] = a.F[(long(e) * K + l) * a.n3 + j];
   double fR = 0.0, fL = 0.0;
   for (int l = 0; l < K; ++l) {
@@ -126,6 +140,11 @@ __global__ __launch_bounds__(256) void k_dg1d_rhs(Dg1dArgs a) {
     double r = (cx * v - phiR[m] * cx * fsR + phiL[m] * cx * fsL) * invJ / w[m];
     const long o = (long(e) * K + m) * a.n3 + j;
     if (a.C) r += a.cscale * a.C[o];
+    if (a.X) {
+      double u = a.cx * a.X[o];
+      if (a.Y) u += a.cy * a.Y[o];
+      r = u + a.cz * r;
+    }
     a.R[o] = r;
   }
 }
@@ -307,8 +326,10 @@ DgLayout dg_layout(qcoll_dg1d d, int rk) {
   return l;
 }
 
-// R = L(F)
-qcoll_status dg1d_rhs(qcoll_dg1d d, const double *F, double *Rout, char *ws, const DgLayout &l, hipStream_t st) {
+// R = L(F), or with x: R = cx x + cy y + cz L(F) (R may be x or y, not F)
+qcoll_status dg1d_rhs(qcoll_dg1d d, const double *F, double *Rout, char *ws, const DgLayout &l, hipStream_t st,
+                      const double *x = nullptr, double cx = 0.0, const double *y = nullptr, double cy = 0.0,
+                      double cz = 1.0) {
   const qcoll::Plan &p = d->plan->p;
   const long n3 = p.n3();
   qcoll_status s;
@@ -336,6 +357,11 @@ qcoll_status dg1d_rhs(qcoll_dg1d d, const double *F, double *Rout, char *ws, con
   qcoll::Dg1dArgs a;
   a.F = F;
   a.R = Rout;
+  a.X = x;
+  a.Y = y;
+  a.cx = cx;
+  a.cy = cy;
+  a.cz = cz;
   a.C = C;
   a.cscale = cscale;
   a.J = d->J;
@@ -355,18 +381,26 @@ qcoll_status dg1d_rhs(qcoll_dg1d d, const double *F, double *Rout, char *ws, con
   a.n3 = n3;
   a.L = p.L;
   a.periodic = d->ends[0].kind == QCOLL_BC_PERIODIC;
-  if (!a.periodic) {
-    qcoll::TimedLaunch tl("dg1d wall", st);
-    hipLaunchKernelGGL(qcoll::k_dg1d_wall, dim3(2), dim3(1024), 0, st, a);
-    if (hipGetLastError() != hipSuccess) return dfail(QCOLL_EDEVICE, "dg1d wall launch failed");
-  }
-  {
+  auto go = [&](auto kc) {
+    constexpr int KC = decltype(kc)::value;
+    if (!a.periodic) {
+      qcoll::TimedLaunch tl("dg1d wall", st);
+      hipLaunchKernelGGL(qcoll::k_dg1d_wall<KC>, dim3(2 * qcoll::kWallSeg), dim3(256), 0, st, a);
+      if (hipGetLastError() != hipSuccess) return dfail(QCOLL_EDEVICE, "dg1d wall launch failed");
+    }
     qcoll::TimedLaunch tl("dg1d transport", st);
-    const long n = long(d->I) * n3;
-    hipLaunchKernelGGL(qcoll::k_dg1d_rhs, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st, a);
+    const int nblk = int((n3 + 255) / 256);
+    hipLaunchKernelGGL(qcoll::k_dg1d_rhs<KC>, dim3(unsigned(d->I) * nblk), dim3(256), 0, st, a, nblk);
     if (hipGetLastError() != hipSuccess) return dfail(QCOLL_EDEVICE, "dg1d transport launch failed");
+    return QCOLL_OK;
+  };
+  switch (d->K) {
+    case 1: return go(std::integral_constant<int, 1>{});
+    case 2: return go(std::integral_constant<int, 2>{});
+    case 3: return go(std::integral_constant<int, 3>{});
+    case 4: return go(std::integral_constant<int, 4>{});
+    default: return go(std::integral_constant<int, 0>{});
   }
-  return QCOLL_OK;
 }
 
 qcoll_status axpby3(double *out, const double *x, double a, const double *y, double b, const double *z, double c,
@@ -497,7 +531,7 @@ qcoll_status qcoll_dg1d_create(qcoll_plan plan, const qcoll_dg1d_params *prm, qc
       return st;
     }
   }
-  if (hipMalloc(&d->nw, 2 * sizeof(double)) != hipSuccess) {
+  if (hipMalloc(&d->nw, 2 * qcoll::kWallSeg * sizeof(double)) != hipSuccess) {
     free_dg1d(d);
     delete d;
     return dfail(QCOLL_ENOMEM, "hipMalloc failed for the wall densities");
@@ -548,15 +582,15 @@ qcoll_status qcoll_dg1d_step(qcoll_dg1d d, double *F, double dt, int32_t rk, voi
   double *v1 = rk >= 2 ? reinterpret_cast<double *>(w + l.off_v1) : nullptr;
   double *v2 = rk >= 3 ? reinterpret_cast<double *>(w + l.off_v2) : nullptr;
   qcoll_status s;
-  if ((s = dg1d_rhs(d, F, Rb, w, l, st)) != QCOLL_OK) return s;
-  if (rk == 1) return axpby3(F, F, 1.0, Rb, dt, nullptr, 0.0, n, st);
+  if (rk == 1) {   // in place: the update waits until every neighbour has read F
+    if ((s = dg1d_rhs(d, F, Rb, w, l, st)) != QCOLL_OK) return s;
+    return axpby3(F, F, 1.0, Rb, dt, nullptr, 0.0, n, st);
+  }
   // SSP-RK2 / SSP-RK3 (Section 3.4)
-  if ((s = axpby3(v1, F, 1.0, Rb, dt, nullptr, 0.0, n, st)) != QCOLL_OK) return s;
-  if ((s = dg1d_rhs(d, v1, Rb, w, l, st)) != QCOLL_OK) return s;
-  if (rk == 2) return axpby3(F, F, 0.5, v1, 0.5, Rb, 0.5 * dt, n, st);
-  if ((s = axpby3(v2, F, 0.75, v1, 0.25, Rb, 0.25 * dt, n, st)) != QCOLL_OK) return s;
-  if ((s = dg1d_rhs(d, v2, Rb, w, l, st)) != QCOLL_OK) return s;
-  return axpby3(F, F, 1.0 / 3.0, v2, 2.0 / 3.0, Rb, 2.0 / 3.0 * dt, n, st);
+  if ((s = dg1d_rhs(d, F, v1, w, l, st, F, 1.0, nullptr, 0.0, dt)) != QCOLL_OK) return s;
+  if (rk == 2) return dg1d_rhs(d, v1, F, w, l, st, F, 0.5, v1, 0.5, 0.5 * dt);
+  if ((s = dg1d_rhs(d, v1, v2, w, l, st, F, 0.75, v1, 0.25, 0.25 * dt)) != QCOLL_OK) return s;
+  return dg1d_rhs(d, v2, F, w, l, st, F, 1.0 / 3.0, v2, 2.0 / 3.0, 2.0 / 3.0 * dt);
 }
 
 }  // extern "C"

@@ -93,9 +93,15 @@ struct grouped_loads<S, std::void_t<decltype(S::kGroupedLoads)>> : std::bool_con
 // computed once.  Lanes of a slab past the end read slab nslab - 1 (always
 // valid) and store nothing.  With SPLIT the real and imaginary parts take
 // turns in one tile.
-template <typename T, int N, int SIGN, class Src, class Dst, int SPB = slab_spb<T, N>(),
-          bool SPLIT = slab_split<T, N>()>
-__global__ __launch_bounds__(256) void k_slab(Src src, Dst dst, long nslab) {
+template <typename T, int N>
+struct SlabTile {
+  T v[slab_split<T, N>() ? 1 : 2][slab_spb<T, N>()][N][N + 1];
+};
+
+template <typename T, int N, int SIGN, class Src, class Dst>
+__device__ __forceinline__ void slab_body(SlabTile<T, N> &tile, const Src &src, const Dst &dst, long nslab) {
+  constexpr int SPB = slab_spb<T, N>();
+  constexpr bool SPLIT = slab_split<T, N>();
   const int s = int(threadIdx.x) / N, c = int(threadIdx.x) % N;
   const long g = long(blockIdx.x) * SPB + s;
   const long gl = g < nslab ? g : nslab - 1;
@@ -122,7 +128,7 @@ __global__ __launch_bounds__(256) void k_slab(Src src, Dst dst, long nslab) {
   fft_reg<N, SIGN, T>(xr, xi);
   if constexpr (SPLIT) {
     // one tile, one component at a time: column -> row, row FFT, row -> column
-    __shared__ T sb[SPB][N][N + 1];
+    auto &sb = tile.v[0];
     const int row = c;
     auto to_rows = [&](T *x) {
       static_for<0, N>([&](auto r) { sb[s][decltype(r)::value][c] = x[decltype(r)::value]; });
@@ -148,8 +154,8 @@ __global__ __launch_bounds__(256) void k_slab(Src src, Dst dst, long nslab) {
     }
     return;
   } else {
-    __shared__ T sre[SPB][N][N + 1];
-    __shared__ T sim[SPB][N][N + 1];
+    auto &sre = tile.v[0];
+    auto &sim = tile.v[1];
     static_for<0, N>([&](auto r) {
       sre[s][decltype(r)::value][c] = xr[decltype(r)::value];
       sim[s][decltype(r)::value][c] = xi[decltype(r)::value];
@@ -172,6 +178,21 @@ __global__ __launch_bounds__(256) void k_slab(Src src, Dst dst, long nslab) {
       });
     }
   }
+}
+
+template <typename T, int N, int SIGN, class Src, class Dst>
+__global__ __launch_bounds__(256) void k_slab(Src src, Dst dst, long nslab) {
+  __shared__ SlabTile<T, N> tile;
+  slab_body<T, N, SIGN>(tile, src, dst, nslab);
+}
+
+// two slab passes of the same size as one launch (blockIdx.y): the gain and the
+// loss inverse of a small batch are launches of a few microseconds each
+template <typename T, int N, int SIGN, class S0, class D0, class S1, class D1>
+__global__ __launch_bounds__(256) void k_slab2(S0 s0, D0 d0, S1 s1, D1 d1, long nslab) {
+  __shared__ SlabTile<T, N> tile;
+  if (blockIdx.y == 0) slab_body<T, N, SIGN>(tile, s0, d0, nslab);
+  else slab_body<T, N, SIGN>(tile, s1, d1, nslab);
 }
 
 // generic pencil kernel: Op(pencil_group, r) with r = j2*N + j3
@@ -309,6 +330,16 @@ struct Passes {
     TimedLaunch tl(what, st);
     constexpr int SPB = slab_spb<T, N>();
     hipLaunchKernelGGL((k_slab<T, N, SIGN, Src, Dst>), dim3(nblk(nslab, SPB)), dim3(SPB * N), 0, st, s, d, nslab);
+    QC_LAUNCH_CHECK(what);
+    return QCOLL_OK;
+  }
+  template <int SIGN, class S0, class D0, class S1, class D1>
+  static qcoll_status slab2(S0 s0, D0 d0, S1 s1, D1 d1, long nslab, hipStream_t st, const char *what) {
+    if (nslab <= 0) return QCOLL_OK;
+    TimedLaunch tl(what, st);
+    constexpr int SPB = slab_spb<T, N>();
+    hipLaunchKernelGGL((k_slab2<T, N, SIGN, S0, D0, S1, D1>), dim3(nblk(nslab, SPB), 2), dim3(SPB * N), 0, st, s0,
+                       d0, s1, d1, nslab);
     QC_LAUNCH_CHECK(what);
     return QCOLL_OK;
   }
