@@ -27,13 +27,23 @@ __device__ __forceinline__ cplx<double> load_c64(__amdgpu_buffer_rsrc_t r, int v
   return cplx<double>{v.x, v.y};
 }
 
+// Words per plane of the LDS tile: at least N (N + 1) for the rows of N + 1 words
+// of the B <-> C transposes, and N more than a multiple of 64, so that the
+// planes that the lanes of one access span (N lanes a plane) continue each
+// other's banks.
+constexpr int tile_stride(int N) {
+  int s = N * (N + 1);
+  while (s % 64 != N % 64) ++s;
+  return s;
+}
+
 template <int N>
 struct FusedGeom {
   // pencils per lane (1: N^2 lanes; the loops below also support 2, which
   // halves the lane count at twice the registers per lane)
   static constexpr int PPL = 1;
   static constexpr int NL = N * N / PPL;
-  static constexpr int S1 = N * N + 32;
+  static constexpr int S1 = tile_stride(N);
   // the B <-> C transposes stay inside a wave when a wave owns whole rows
   // (64 lanes = 64/N rows of N lanes, one pencil per lane)
   static constexpr bool WAVE_BC = (PPL == 1) && (64 % N == 0);
