@@ -70,6 +70,31 @@ double sinc(double z) { return z == 0.0 ? 1.0 : std::sin(z) / z; }
 
 int kappa(int n, int N) { return n < N / 2 ? n : n - N; }
 
+// x.x, y.y and x.y in eight fixed partial sums each (one running sum is a chain
+// of dependent additions, which set the time of a truncated plan's creation)
+void dots(const double *x, const double *y, long n, double &a, double &b, double &c) {
+  constexpr int W = 8;
+  double sa[W] = {}, sb[W] = {}, sc[W] = {};
+  long k = 0;
+  for (; k + W <= n; k += W)
+    for (int l = 0; l < W; ++l) {
+      sa[l] += x[k + l] * x[k + l];
+      sb[l] += y[k + l] * y[k + l];
+      sc[l] += x[k + l] * y[k + l];
+    }
+  for (int l = 0; k < n; ++k, ++l) {
+    sa[l] += x[k] * x[k];
+    sb[l] += y[k] * y[k];
+    sc[l] += x[k] * y[k];
+  }
+  a = b = c = 0.0;
+  for (int l = 0; l < W; ++l) {
+    a += sa[l];
+    b += sb[l];
+    c += sc[l];
+  }
+}
+
 // One-sided Jacobi: rotate the rows of A [m][n] until pairwise orthogonal.
 // On return A holds J A (orthogonal rows) and J [m][m] the accumulated rotation.
 void jacobi_rows(std::vector<double> &A, int m, long n, std::vector<double> &J) {
@@ -79,13 +104,10 @@ void jacobi_rows(std::vector<double> &A, int m, long n, std::vector<double> &J) 
     double off = 0.0;
     for (int i = 0; i < m - 1; ++i) {
       for (int j = i + 1; j < m; ++j) {
-        double *ri = &A[size_t(i) * n], *rj = &A[size_t(j) * n];
-        double a = 0, b = 0, c = 0;
-        for (long k = 0; k < n; ++k) {
-          a += ri[k] * ri[k];
-          b += rj[k] * rj[k];
-          c += ri[k] * rj[k];
-        }
+        double *__restrict__ ri = &A[size_t(i) * n];
+        double *__restrict__ rj = &A[size_t(j) * n];
+        double a, b, c;
+        dots(ri, rj, n, a, b, c);
         if (a == 0.0 || b == 0.0) continue;
         double rel = std::fabs(c) / std::sqrt(a * b);
         off = std::max(off, rel);
