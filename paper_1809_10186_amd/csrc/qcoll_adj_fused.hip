@@ -41,7 +41,13 @@ constexpr int pow2_floor(int n) {
 template <int N>
 struct AdjGeom {
   static constexpr int H1 = N / 2 + 1;
-  static constexpr size_t tile = size_t(N) * FusedGeom<N>::S1;
+  // both components in the tile from 16^3 on (8 nodes, M 12, with the omega
+  // gradient: 400 items at 24^3 2866 -> 2419 us, 1024 at 16^3 1204 -> 1189); a
+  // workgroup of 8^3 is one wave and of 12^3 three, whose barriers are cheap and
+  // whose tile would be most of their LDS (4096 at 8^3 1370 -> 1397, 2048 at
+  // 12^3 1600 -> 1644)
+  static constexpr bool BOTH = FusedGeom<N>::BOTH && N >= 16;
+  static constexpr size_t tile = size_t(N) * FusedGeom<N>::S1 * (BOTH ? 2 : 1);
   static constexpr size_t exch = size_t(2) * H1 * N * N;
   static constexpr size_t work = tile > exch ? tile : exch;   // floats
   // after the work area: the axis-1 shift factors b1 of every q of the pair
@@ -87,10 +93,32 @@ __global__ __launch_bounds__(FusedGeom<N>::NL) void k_adj_fused(const cplx<float
   auto ra1 = [&](int, int i) { return hi * S1 + i * N + lo; };
   auto wa2 = [&](int, int i) { return hi * S1 + lo * (N + 1) + i; };
   auto ra2 = [&](int, int i) { return hi * S1 + i * (N + 1) + lo; };
+  // BOTH: each pencil goes where the lane read the one before
+  constexpr bool BOTH = AdjGeom<N>::BOTH;
+  const TileAt<N> at{hi, lo}, atp{partner / N, partner % N};
+  auto pa = [=](int i) { return at.a(i); };
+  auto pb = [=](int i) { return at.b(i); };
+  auto pc = [=](int i) { return at.c(i); };
   // B <-> C: within each wave's own rows when a wave owns whole rows
   auto transpose_bc = [&](float(*v)[N], auto wa, auto ra) {
     if constexpr (G::WAVE_BC) lds_transpose_wave<N, 1>(lds, v, wa, ra);
     else lds_transpose<N, 1>(lds, v, wa, ra);
+  };
+  auto order_bc = [] {
+    if constexpr (G::WAVE_BC) lds_wave_order();
+    else __syncthreads();
+  };
+  // A -> B and B -> C of both components; the tile must be free for the lane's
+  // own pencil
+  auto both_ab = [&](float *zr, float *zi) {
+    tile_put<N>(lds, zr, zi, pa);
+    __syncthreads();
+    tile_get<N>(lds, zr, zi, pb);
+  };
+  auto both_bc = [&](float *zr, float *zi) {
+    tile_put<N>(lds, zr, zi, pb);
+    order_bc();
+    tile_get<N>(lds, zr, zi, pc);
   };
 
   {
@@ -107,11 +135,19 @@ __global__ __launch_bounds__(FusedGeom<N>::NL) void k_adj_fused(const cplx<float
       zi[0][kk] = v.im * a;
     });
     fft_reg<N, +1, float>(zr[0], zi[0]);
-    lds_transpose<N, 1>(lds, zr, wa1, ra1);
-    lds_transpose<N, 1>(lds, zi, wa1, ra1);
+    if constexpr (BOTH) {
+      both_ab(zr[0], zi[0]);
+    } else {
+      lds_transpose<N, 1>(lds, zr, wa1, ra1);
+      lds_transpose<N, 1>(lds, zi, wa1, ra1);
+    }
     fft_reg<N, +1, float>(zr[0], zi[0]);
-    transpose_bc(zr, wa2, ra2);
-    transpose_bc(zi, wa2, ra2);
+    if constexpr (BOTH) {
+      both_bc(zr[0], zi[0]);
+    } else {
+      transpose_bc(zr, wa2, ra2);
+      transpose_bc(zi, wa2, ra2);
+    }
     fft_reg<N, +1, float>(zr[0], zi[0]);
     // h_p is real (alpha_p even and real, g real): keep the real part
     float *ho = Hp + bp * n3 + long(lane) * N;
@@ -177,19 +213,21 @@ __global__ __launch_bounds__(FusedGeom<N>::NL) void k_adj_fused(const cplx<float
     // A -> B writes of this term (stage A above reads only the b1 rows, which
     // the loop never writes)
     __syncthreads();
-    // A -> B across waves; when the B -> C transpose after it stays in own
-    // rows, the barrier after the imaginary-part reads is not needed
-    lds_transpose<N, 1>(lds, zr, wa1, ra1);
-    if constexpr (G::WAVE_BC) {
-      static_for<0, N>([&](auto i) { lds[wa1(0, decltype(i)::value)] = zi[0][decltype(i)::value]; });
-      __syncthreads();
-      static_for<0, N>([&](auto i) { zi[0][decltype(i)::value] = lds[ra1(0, decltype(i)::value)]; });
+    if constexpr (BOTH) {
+      both_ab(zr[0], zi[0]);
     } else {
-      lds_transpose<N, 1>(lds, zi, wa1, ra1);
+      // when the B -> C transpose after it stays in own rows, the barrier after
+      // the imaginary-part reads is not needed
+      lds_transpose<N, 1>(lds, zr, wa1, ra1);
+      lds_transpose<N, 1, !G::WAVE_BC>(lds, zi, wa1, ra1);
     }
     fft_reg<N, +1, float>(zr[0], zi[0]);
-    transpose_bc(zr, wa2, ra2);
-    transpose_bc(zi, wa2, ra2);
+    if constexpr (BOTH) {
+      both_bc(zr[0], zi[0]);
+    } else {
+      transpose_bc(zr, wa2, ra2);
+      transpose_bc(zi, wa2, ra2);
+    }
     fft_reg<N, +1, float>(zr[0], zi[0]);
     // lane (j1, j2) holds u(j1, j2, :): y = w_q h_p conj(u)
     const float w = wq[q];
@@ -211,11 +249,23 @@ __global__ __launch_bounds__(FusedGeom<N>::NL) void k_adj_fused(const cplx<float
     if constexpr (DW) dot += double(w) * double(part);
     // forward transform: axis 3 here, C -> B (own rows), axis 2, B -> A (across waves), axis 1
     fft_reg<N, -1, float>(zr[0], zi[0]);
-    transpose_bc(zr, ra2, wa2);
-    transpose_bc(zi, ra2, wa2);
+    if constexpr (BOTH) {
+      tile_put<N>(lds, zr[0], zi[0], pc);
+      order_bc();
+      tile_get<N>(lds, zr[0], zi[0], pb);
+    } else {
+      transpose_bc(zr, ra2, wa2);
+      transpose_bc(zi, ra2, wa2);
+    }
     fft_reg<N, -1, float>(zr[0], zi[0]);
-    lds_transpose<N, 1>(lds, zr, ra1, wa1);
-    lds_transpose<N, 1, false>(lds, zi, ra1, wa1);   // closing barrier: before the exchange writes
+    if constexpr (BOTH) {
+      tile_put<N>(lds, zr[0], zi[0], pb);
+      __syncthreads();
+      tile_get<N>(lds, zr[0], zi[0], pa);
+    } else {
+      lds_transpose<N, 1>(lds, zr, ra1, wa1);
+      lds_transpose<N, 1, false>(lds, zi, ra1, wa1);   // closing barrier: before the exchange writes
+    }
     fft_reg<N, -1, float>(zr[0], zi[0]);
     // lane (k2, k3): c_s(k) P(k), then the values at k1 = -s (s = 0..N/2) to the partner
     static_for<0, N>([&](auto k) {
@@ -225,19 +275,35 @@ __global__ __launch_bounds__(FusedGeom<N>::NL) void k_adj_fused(const cplx<float
       zr[0][kk] *= c;
       zi[0][kk] *= c;
     });
-    __syncthreads();
-    static_for<0, H1>([&](auto s) {
-      constexpr int ss = decltype(s)::value;
-      constexpr int src = (N - ss) % N;
-      lds[ss * NL + lane] = zr[0][src];
-      lds[(H1 + ss) * NL + lane] = zi[0][src];
-    });
-    __syncthreads();
-    static_for<0, H1>([&](auto s) {
-      constexpr int ss = decltype(s)::value;
-      acc[2 * ss] += zr[0][ss] + lds[ss * NL + partner];
-      acc[2 * ss + 1] += zi[0][ss] - lds[(H1 + ss) * NL + partner];
-    });
+    if constexpr (BOTH) {
+      // into the pencil's own places again, which only this lane has read
+      float2 *l = reinterpret_cast<float2 *>(lds);
+      static_for<0, H1>([&](auto s) {
+        constexpr int src = (N - decltype(s)::value) % N;
+        l[pa(src)] = make_float2(zr[0][src], zi[0][src]);
+      });
+      __syncthreads();
+      static_for<0, H1>([&](auto s) {
+        constexpr int ss = decltype(s)::value;
+        const float2 v = l[atp.a((N - ss) % N)];
+        acc[2 * ss] += zr[0][ss] + v.x;
+        acc[2 * ss + 1] += zi[0][ss] - v.y;
+      });
+    } else {
+      __syncthreads();
+      static_for<0, H1>([&](auto s) {
+        constexpr int ss = decltype(s)::value;
+        constexpr int src = (N - ss) % N;
+        lds[ss * NL + lane] = zr[0][src];
+        lds[(H1 + ss) * NL + lane] = zi[0][src];
+      });
+      __syncthreads();
+      static_for<0, H1>([&](auto s) {
+        constexpr int ss = decltype(s)::value;
+        acc[2 * ss] += zr[0][ss] + lds[ss * NL + partner];
+        acc[2 * ss + 1] += zi[0][ss] - lds[(H1 + ss) * NL + partner];
+      });
+    }
   }
   cplx<float> *zo = Zh + bp * (long(H1) * n2);
   static_for<0, H1>([&](auto s) {

@@ -47,12 +47,56 @@ struct FusedGeom {
   // the B <-> C transposes stay inside a wave when a wave owns whole rows
   // (64 lanes = 64/N rows of N lanes, one pencil per lane)
   static constexpr bool WAVE_BC = (PPL == 1) && (64 % N == 0);
-  static constexpr size_t lds_bytes = size_t(N) * S1 * sizeof(float);
-  // waves per SIMD the register budget must allow: at N = 24 a workgroup is 9
-  // waves with a 57 KiB tile, and 5 waves per SIMD let two workgroups share a
-  // CU (their barrier phases then overlap); elsewhere no constraint
-  static constexpr int WPE = (N == 24) ? 5 : 1;
+  // Below 32 the tile holds both components (N = 24: 112.5 KiB; at 32 it would
+  // be 264 KiB, so there the real parts move first, then the imaginary parts).
+  // With element (a, b, c) at a S1 + b (N + 1) + c throughout, a lane writes each
+  // pencil where it read the one before, and a transpose costs one barrier
+  // instead of the four of two components in turn.  It pays although one
+  // workgroup of 24^3 then has a CU to itself: 1024 items x 4 nodes, M 6, in
+  // 1029 us before (two workgroups of 57 KiB a CU), 1021 without the second,
+  // 979 with both components, 878 with pencils written in place, 850 with the
+  // components side by side (8-byte accesses).
+  static constexpr bool BOTH = N < 32;
+  static constexpr size_t lds_bytes = size_t(N) * S1 * (BOTH ? sizeof(float2) : sizeof(float));
+  // waves per SIMD the register budget must allow: the 9 waves of 24^3
+  static constexpr int WPE = (N == 24) ? 3 : 1;
 };
+
+// element addresses of the tile for lane (hi, lo): its pencil along the first,
+// second or third index
+template <int N>
+struct TileAt {
+  static constexpr int S1 = FusedGeom<N>::S1, R = N + 1;
+  int hi, lo;
+  __device__ __forceinline__ int a(int i) const { return i * S1 + hi * R + lo; }
+  __device__ __forceinline__ int b(int i) const { return hi * S1 + i * R + lo; }
+  __device__ __forceinline__ int c(int i) const { return hi * S1 + lo * R + i; }
+};
+
+// orders a wave's LDS writes before its reads of what its other lanes wrote
+__device__ __forceinline__ void lds_wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// both components of the lane's pencil into / out of the tile
+template <int N, class AT>
+__device__ __forceinline__ void tile_put(float *lds, const float *zr, const float *zi, AT at) {
+  float2 *l = reinterpret_cast<float2 *>(lds);
+  static_for<0, N>([&](auto i) {
+    l[at(decltype(i)::value)] = make_float2(zr[decltype(i)::value], zi[decltype(i)::value]);
+  });
+}
+template <int N, class AT>
+__device__ __forceinline__ void tile_get(const float *lds, float *zr, float *zi, AT at) {
+  const float2 *l = reinterpret_cast<const float2 *>(lds);
+  static_for<0, N>([&](auto i) {
+    const float2 v = l[at(decltype(i)::value)];
+    zr[decltype(i)::value] = v.x;
+    zi[decltype(i)::value] = v.y;
+  });
+}
 
 // move one component (re or im) of every pencil of the lane through LDS; with
 // TAIL = false the barrier after the reads is left to the caller (the tile
@@ -84,17 +128,13 @@ __device__ __forceinline__ void lds_transpose_wave(float *lds, float (*v)[N], WA
       lds[wa(decltype(u)::value, decltype(i)::value)] = v[decltype(u)::value][decltype(i)::value];
     });
   });
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  lds_wave_order();
   static_for<0, PPL>([&](auto u) {
     static_for<0, N>([&](auto i) {
       v[decltype(u)::value][decltype(i)::value] = lds[ra(decltype(u)::value, decltype(i)::value)];
     });
   });
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  lds_wave_order();
 }
 
 // XCD-aware block numbering: hardware block i runs on XCD i % 8; logical

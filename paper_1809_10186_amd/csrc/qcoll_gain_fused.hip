@@ -18,10 +18,13 @@
 // The forward transform of A_p runs the same stages backwards and stores
 // W_p[k1][k2][k3] for k1 <= N/2 from lane (k2, k3), coalesced (the other
 // planes follow by Hermitian symmetry).
-// Each transpose moves the real parts, then the imaginary parts, through one
-// LDS tile of N * (N^2 + 32) floats (135 KiB at N = 32).  The padding makes
-// both the writes and the reads of each transpose free of bank conflicts at
-// N = 32.  Workgroups are renumbered so that consecutive (item, node) pairs
+// Each transpose moves both components through one LDS tile, in place (N < 32:
+// FusedGeom), or the real parts, then the imaginary parts (N = 32, 132 KiB).  The
+// padding makes both the writes and the reads of each transpose free of bank
+// conflicts.  The loop is bound by VALU issue and LDS in turn, with the
+// transposes' barriers between them: 1024 items x 4 nodes at 24^3, M 6, 1029 ->
+// 850 us with the tile of both components, VSS 400 items x 8 nodes, M 12, 2269 ->
+// 1655 (whole call).  Workgroups are renumbered so that consecutive (item, node) pairs
 // run on the same XCD and share the item's spectrum in that XCD's L2.
 #include <hip/hip_runtime.h>
 
@@ -101,6 +104,19 @@ __global__ __launch_bounds__(FusedGeom<N>::NL, FusedGeom<N>::WPE) void k_gain_fu
   auto ra1 = [&](int u, int i) { return hi[u] * S1 + i * N + lo[u]; };
   auto wa2 = [&](int u, int i) { return hi[u] * S1 + lo[u] * (N + 1) + i; };
   auto ra2 = [&](int u, int i) { return hi[u] * S1 + i * (N + 1) + lo[u]; };
+  // N < 32: both components in the tile, each pencil written where the lane
+  // read the one before
+  constexpr bool BOTH = G::BOTH;
+  static_assert(!BOTH || PPL == 1, "one pencil per lane");
+  const TileAt<N> at0{hi[0], lo[0]};
+  auto pa = [=](int i) { return at0.a(i); };
+  auto pb = [=](int i) { return at0.b(i); };
+  auto pc = [=](int i) { return at0.c(i); };
+  // between stages B and C: inside a wave when it owns whole rows
+  auto order_bc = [] {
+    if constexpr (G::WAVE_BC) lds_wave_order();
+    else __syncthreads();
+  };
 
   const __amdgpu_buffer_rsrc_t hr = make_rsrc(H + b * n3, unsigned(n3 * sizeof(cplx<float>)));
   const int q0 = MODE == 1 ? int(lb % M) : 0;
@@ -158,8 +174,12 @@ __global__ __launch_bounds__(FusedGeom<N>::NL, FusedGeom<N>::WPE) void k_gain_fu
     // reach other waves' rows; stage A above touches no LDS, so the barrier
     // sits here and a wave that is done with the previous term starts the
     // next term's loads and first transform while others finish theirs.
-    if constexpr (G::WAVE_BC || VSS) __syncthreads();
-    if constexpr (G::WAVE_BC) {
+    if constexpr (!(BOTH && VSS)) __syncthreads();   // that loop ends with reads of the lane's own pencil
+    if constexpr (BOTH) {
+      tile_put<N>(lds, zr[0], zi[0], pa);
+      __syncthreads();
+      tile_get<N>(lds, zr[0], zi[0], pb);
+    } else {
       // A -> B crosses waves: barrier after the writes; the barrier after the
       // imaginary-part reads is not needed (B -> C below stays in own rows)
       lds_transpose<N, PPL>(lds, zr, wa1, ra1);
@@ -174,18 +194,16 @@ __global__ __launch_bounds__(FusedGeom<N>::NL, FusedGeom<N>::WPE) void k_gain_fu
           zi[decltype(u)::value][decltype(i)::value] = lds[ra1(decltype(u)::value, decltype(i)::value)];
         });
       });
-    } else {
-      lds_transpose<N, PPL>(lds, zr, wa1, ra1);
-      lds_transpose<N, PPL>(lds, zi, wa1, ra1);
     }
     static_for<0, PPL>([&](auto u) { fft_reg<N, +1, float>(zr[decltype(u)::value], zi[decltype(u)::value]); });
-    // B -> C: element (j1, j2, k3) at j1*S1 + k3*(N+1) + j2
-    if constexpr (G::WAVE_BC) {
+    // B -> C: element (j1, j2, k3) at j1*S1 + k3*(N+1) + j2 (N < 32: j2*(N+1) + k3)
+    if constexpr (BOTH) {
+      tile_put<N>(lds, zr[0], zi[0], pb);
+      order_bc();
+      tile_get<N>(lds, zr[0], zi[0], pc);
+    } else {
       lds_transpose_wave<N, PPL>(lds, zr, wa2, ra2);
       lds_transpose_wave<N, PPL>(lds, zi, wa2, ra2);
-    } else {
-      lds_transpose<N, PPL>(lds, zr, wa2, ra2);
-      lds_transpose<N, PPL>(lds, zi, wa2, ra2);
     }
     if constexpr (MODE == 1) {
       static_for<0, PPL>([&](auto uu) {
@@ -230,16 +248,23 @@ __global__ __launch_bounds__(FusedGeom<N>::NL, FusedGeom<N>::WPE) void k_gain_fu
         fft_reg<N, -1, float>(zr[u], zi[u]);
       });
       // C -> B (own rows), axis 2; B -> A (across waves), axis 1
-      if constexpr (G::WAVE_BC) {
+      if constexpr (BOTH) {
+        tile_put<N>(lds, zr[0], zi[0], pc);
+        order_bc();
+        tile_get<N>(lds, zr[0], zi[0], pb);
+      } else {
         lds_transpose_wave<N, PPL>(lds, zr, ra2, wa2);
         lds_transpose_wave<N, PPL>(lds, zi, ra2, wa2);
-      } else {
-        lds_transpose<N, PPL>(lds, zr, ra2, wa2);
-        lds_transpose<N, PPL>(lds, zi, ra2, wa2);
       }
       static_for<0, PPL>([&](auto u) { fft_reg<N, -1, float>(zr[decltype(u)::value], zi[decltype(u)::value]); });
-      lds_transpose<N, PPL>(lds, zr, ra1, wa1);
-      lds_transpose<N, PPL, false>(lds, zi, ra1, wa1);   // closing barrier: before the next A -> B
+      if constexpr (BOTH) {
+        tile_put<N>(lds, zr[0], zi[0], pb);
+        __syncthreads();
+        tile_get<N>(lds, zr[0], zi[0], pa);
+      } else {
+        lds_transpose<N, PPL>(lds, zr, ra1, wa1);
+        lds_transpose<N, PPL, false>(lds, zi, ra1, wa1);   // closing barrier: before the next A -> B
+      }
       const float *a = apq + size_t(p * M + q) * (size_t(H1) * n2);
       static_for<0, PPL>([&](auto uu) {
         constexpr int u = decltype(uu)::value;
@@ -282,7 +307,12 @@ __global__ __launch_bounds__(FusedGeom<N>::NL, FusedGeom<N>::WPE) void k_gain_fu
       hi[decltype(u)::value] = t / N;
       lo[decltype(u)::value] = t % N;
     });
-    if constexpr (G::WAVE_BC && MODE == 0) __syncthreads();
+    const TileAt<N> at1{hi[0], lo[0]};
+    auto qa = [=](int i) { return at1.a(i); };
+    auto qb = [=](int i) { return at1.b(i); };
+    auto qc = [=](int i) { return at1.c(i); };
+    // N < 32: the last reads were of the lane's own pencil, which it writes next
+    if constexpr (!BOTH && MODE == 0) __syncthreads();
     float zr[PPL][N], zi[PPL][N];
     static_for<0, PPL>([&](auto uu) {
       constexpr int u = decltype(uu)::value;
@@ -292,11 +322,23 @@ __global__ __launch_bounds__(FusedGeom<N>::NL, FusedGeom<N>::WPE) void k_gain_fu
       });
       fft_reg<N, -1, float>(zr[u], zi[u]);
     });
-    lds_transpose<N, PPL>(lds, zr, ra2, wa2);
-    lds_transpose<N, PPL>(lds, zi, ra2, wa2);
+    if constexpr (BOTH) {
+      tile_put<N>(lds, zr[0], zi[0], qc);
+      order_bc();
+      tile_get<N>(lds, zr[0], zi[0], qb);
+    } else {
+      lds_transpose<N, PPL>(lds, zr, ra2, wa2);
+      lds_transpose<N, PPL>(lds, zi, ra2, wa2);
+    }
     static_for<0, PPL>([&](auto u) { fft_reg<N, -1, float>(zr[decltype(u)::value], zi[decltype(u)::value]); });
-    lds_transpose<N, PPL>(lds, zr, ra1, wa1);
-    lds_transpose<N, PPL>(lds, zi, ra1, wa1);
+    if constexpr (BOTH) {
+      tile_put<N>(lds, zr[0], zi[0], qb);
+      __syncthreads();
+      tile_get<N>(lds, zr[0], zi[0], qa);
+    } else {
+      lds_transpose<N, PPL>(lds, zr, ra1, wa1);
+      lds_transpose<N, PPL>(lds, zi, ra1, wa1);
+    }
     // W_p is Hermitian (A_p is real, alpha is even in k): only the planes
     // k1 <= N/2 are stored, compactly, (N/2 + 1) N^2 values per pair
     const float *ae = alpha_eff + long(p) * n3;
