@@ -252,7 +252,7 @@ qcoll_status qcoll_eval_bilinear(qcoll_plan plan, int64_t batch, const double *f
     return a < (const void *)(Q + batch * n3) && (const void *)Q < (const void *)((const double *)a + batch * n3);
   };
   if (overlap(f) || overlap(g)) return fail(QCOLL_EINVAL, "Q must not overlap f or g");
-  const qcoll::Layout lay = qcoll::make_layout(plan->p, batch, 2);
+  const qcoll::Layout lay = qcoll::make_layout(plan->p, batch, 2, 0, ws_bytes);
   if (!ws || ws_bytes < lay.total) return fail(QCOLL_EWORKSPACE, "workspace missing or smaller than qcoll_workspace_bytes(op 2)");
   qcoll_status st = check_device(plan->p);
   if (st != QCOLL_OK) return st;
@@ -293,7 +293,7 @@ qcoll_status qcoll_vjp(qcoll_plan plan, int64_t batch, const double *f, const do
   if (!df && !domega) return QCOLL_OK;
   if (domega && plan->p.truncated)
     return fail(QCOLL_ENOTSUP, "the omega gradient needs an untruncated plan (svd_rank < 0)");
-  const qcoll::Layout lay = qcoll::make_layout(plan->p, batch, 1);
+  const qcoll::Layout lay = qcoll::make_layout(plan->p, batch, 1, 0, ws_bytes);
   if (!ws || ws_bytes < lay.total) return fail(QCOLL_EWORKSPACE, "workspace missing or smaller than qcoll_workspace_bytes");
   const long n3 = plan->p.n3();
   if (df && (((const void *)df < (const void *)(f + batch * n3) && (const void *)f < (const void *)(df + batch * n3)) ||
@@ -416,12 +416,14 @@ qcoll_status qcoll_dg_collide_svd(qcoll_plan plan, int64_t n_elem, int32_t K, in
   const size_t n3 = size_t(plan->p.n3());
   const size_t terms = size_t(n_elem) * R;
   if (terms > size_t(0x7fffffff)) return fail(QCOLL_EINVAL, "n_elem * R too large");
-  if (!ws || ws_bytes < qcoll_dg_svd_workspace_bytes(plan, n_elem, K, R))
+  auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
+  const size_t vol = al(terms * n3 * sizeof(double));
+  const qcoll::Layout lay =
+      qcoll::make_layout(plan->p, int64_t(terms), 2, 0, ws_bytes > 3 * vol ? ws_bytes - 3 * vol : 0);
+  if (!ws || ws_bytes < 3 * vol + lay.total)
     return fail(QCOLL_EWORKSPACE, "workspace missing or smaller than qcoll_dg_svd_workspace_bytes");
   qcoll_status st = check_device(plan->p);
   if (st != QCOLL_OK) return st;
-  auto al = [](size_t x) { return (x + 255) & ~size_t(255); };
-  const size_t vol = al(terms * n3 * sizeof(double));
   char *w = static_cast<char *>(ws);
   double *Hf = reinterpret_cast<double *>(w);
   double *Hg = reinterpret_cast<double *>(w + vol);
@@ -430,7 +432,6 @@ qcoll_status qcoll_dg_collide_svd(qcoll_plan plan, int64_t n_elem, int32_t K, in
   hipStream_t s = static_cast<hipStream_t>(stream);
   if ((st = qcoll::launch_dg_contract(T1, F, Hf, n_elem, R, K, long(n3), s)) != QCOLL_OK) return st;
   if ((st = qcoll::launch_dg_contract(T2, F, Hg, n_elem, R, K, long(n3), s)) != QCOLL_OK) return st;
-  const qcoll::Layout lay = qcoll::make_layout(plan->p, int64_t(terms), 2);
   if ((st = qcoll::launch_eval2(plan->p, int64_t(terms), Hf, Hg, Qd, ews, lay, s)) != QCOLL_OK) return st;
   if (conserve && (st = qcoll::launch_conserve(plan->p, int64_t(terms), Qd, nullptr, s)) != QCOLL_OK) return st;
   return qcoll::launch_dg_contract(W, Qd, C, n_elem, K, R, long(n3), s);

@@ -53,6 +53,7 @@ struct qcoll_group_s {
     std::vector<uint64_t> gens;   // plan generations at capture
     int32_t op = 0, flag = 0;
     void *ws = nullptr;
+    bool small = false;
     hipStream_t st = nullptr;
     hipGraphExec_t exec = nullptr;
   };
@@ -61,21 +62,33 @@ struct qcoll_group_s {
 
 namespace {
 
-size_t plan_bytes(const qcoll::Plan &p, int64_t count, int32_t op) {
+// small: the plans without a chunk of their own in the chunks that any workspace
+// holds that was sized for fewer items
+long plan_chunk(const qcoll::Plan &p, int32_t op, bool small) {
+  return small && (op == 1 || p.chunk == 0) ? qcoll::least_chunk(p, op) : 0;
+}
+
+size_t plan_bytes(const qcoll::Plan &p, int64_t count, int32_t op, bool small) {
   if (count <= 0) return 0;
-  return al256(qcoll::make_layout(p, count, op).total);
+  return al256(qcoll::make_layout(p, count, op, plan_chunk(p, op, small)).total);
+}
+
+size_t group_bytes(qcoll_group g, int32_t op, bool small) {
+  size_t o = 0;
+  for (size_t i = 0; i < g->plans.size(); ++i) o += plan_bytes(g->plans[i]->p, g->counts[i], op, small);
+  return o;
 }
 
 // enqueue every branch of the group on its stream, fork/join on st
 qcoll_status enqueue(qcoll_group g, int32_t op, const double *const *a, const double *const *b,
-                     double *const *out, double *const *out2, int32_t flag, void *ws, hipStream_t st) {
+                     double *const *out, double *const *out2, int32_t flag, void *ws, bool small, hipStream_t st) {
   if (hipEventRecord(g->fork, st) != hipSuccess) return gfail(QCOLL_EDEVICE, "hipEventRecord failed");
   char *w = static_cast<char *>(ws);
   std::vector<size_t> off(g->plans.size());
   size_t o = 0;
   for (size_t i = 0; i < g->plans.size(); ++i) {
     off[i] = o;
-    o += plan_bytes(g->plans[i]->p, g->counts[i], op);
+    o += plan_bytes(g->plans[i]->p, g->counts[i], op, small);
   }
   for (int i : g->order) {
     const qcoll::Plan &p = g->plans[i]->p;
@@ -83,7 +96,7 @@ qcoll_status enqueue(qcoll_group g, int32_t op, const double *const *a, const do
     if (n == 0) continue;
     hipStream_t s = g->streams[i];
     if (hipStreamWaitEvent(s, g->fork, 0) != hipSuccess) return gfail(QCOLL_EDEVICE, "hipStreamWaitEvent failed");
-    const qcoll::Layout lay = qcoll::make_layout(p, n, op);
+    const qcoll::Layout lay = qcoll::make_layout(p, n, op, plan_chunk(p, op, small));
     qcoll_status rc;
     if (op == 0) {
       if ((rc = qcoll::launch_eval(p, n, a[i], out[i], w + off[i], lay, s)) != QCOLL_OK) return rc;
@@ -102,7 +115,9 @@ qcoll_status enqueue(qcoll_group g, int32_t op, const double *const *a, const do
 qcoll_status run(qcoll_group g, int32_t op, const double *const *a, const double *const *b, double *const *out,
                  double *const *out2, int32_t flag, void *ws, size_t ws_bytes, void *stream, int32_t use_graph) {
   if (!g) return gfail(QCOLL_EINVAL, "group is NULL");
-  const size_t need = qcoll_group_workspace_bytes(g, op);
+  const size_t most = group_bytes(g, op, false);
+  const bool small = ws_bytes < most;
+  const size_t need = small ? group_bytes(g, op, true) : most;
   if (need && (!ws || ws_bytes < need)) return gfail(QCOLL_EWORKSPACE, "workspace missing or too small");
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev != g->device) return gfail(QCOLL_EINVAL, "wrong current device");
@@ -112,7 +127,7 @@ qcoll_status run(qcoll_group g, int32_t op, const double *const *a, const double
       return gfail(QCOLL_EINVAL, "NULL array for a plan with items");
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (!use_graph) return enqueue(g, op, a, b, out, out2, flag, ws, st);
+  if (!use_graph) return enqueue(g, op, a, b, out, out2, flag, ws, small, st);
 
   // a captured graph bakes in the plans' table pointers, schedules and
   // workspace layouts: the key holds every plan's generation besides the I/O
@@ -128,7 +143,8 @@ qcoll_status run(qcoll_group g, int32_t op, const double *const *a, const double
     gens.push_back(g->plans[i]->p.gen);
   }
   for (auto &c : g->cache)
-    if (c.ptrs == key && c.gens == gens && c.op == op && c.flag == flag && c.ws == ws && c.st == st) {
+    if (c.ptrs == key && c.gens == gens && c.op == op && c.flag == flag && c.ws == ws && c.small == small &&
+        c.st == st) {
       if (hipGraphLaunch(c.exec, st) != hipSuccess) return gfail(QCOLL_EDEVICE, "hipGraphLaunch failed");
       return QCOLL_OK;
     }
@@ -139,7 +155,7 @@ qcoll_status run(qcoll_group g, int32_t op, const double *const *a, const double
     qcoll_timing_enable(timing);
     return gfail(QCOLL_EDEVICE, "hipStreamBeginCapture failed (the default stream cannot be captured)");
   }
-  qcoll_status rc = enqueue(g, op, a, b, out, out2, flag, ws, st);
+  qcoll_status rc = enqueue(g, op, a, b, out, out2, flag, ws, small, st);
   hipGraph_t graph = nullptr;
   const hipError_t ec = hipStreamEndCapture(st, &graph);
   qcoll_timing_enable(timing);
@@ -164,6 +180,7 @@ qcoll_status run(qcoll_group g, int32_t op, const double *const *a, const double
   c.op = op;
   c.flag = flag;
   c.ws = ws;
+  c.small = small;
   c.st = st;
   c.exec = exec;
   g->cache.push_back(c);
@@ -227,9 +244,7 @@ qcoll_status qcoll_group_destroy(qcoll_group g) {
 
 size_t qcoll_group_workspace_bytes(qcoll_group g, int32_t op) {
   if (!g || (op != 0 && op != 1)) return 0;
-  size_t o = 0;
-  for (size_t i = 0; i < g->plans.size(); ++i) o += plan_bytes(g->plans[i]->p, g->counts[i], op);
-  return o;
+  return group_bytes(g, op, false);
 }
 
 qcoll_status qcoll_group_eval(qcoll_group g, const double *const *f, double *const *Q, int32_t conserve, void *ws,
@@ -266,10 +281,16 @@ qcoll_status qcoll_plan_set_chunk(qcoll_plan plan, int32_t items) {
 
 // candidate items per chunk of the autotuner: each nominal size c is
 // balanced over the batch, ceil(batch / ceil(batch / c)), so that all
-// launches of one eval have the same size; duplicates are dropped
-static std::vector<int> tune_chunks(int64_t batch) {
+// launches of one eval have the same size; duplicates are dropped.  A larger
+// default chunk (small grids) is one of them where the workspace holds it.
+static std::vector<int> tune_chunks(qcoll::Plan p, int sch, int64_t batch, size_t ws_bytes) {
   std::vector<int> out;
-  for (int c : {32, 64, 96, 128, 192, 256}) {
+  std::vector<int> sizes{32, 64, 96, 128, 192, 256};
+  p.schedule = sch;
+  p.chunk = int(qcoll::eval_chunk(p));
+  if (p.chunk > sizes.back() && batch > sizes.back() && qcoll::make_layout(p, batch, 0, 0, ws_bytes).total <= ws_bytes)
+    sizes.push_back(p.chunk);
+  for (int c : sizes) {
     const int64_t n = (batch + c - 1) / c;
     const int ck = int((batch + n - 1) / n);
     if (std::find(out.begin(), out.end(), ck) == out.end()) out.push_back(ck);
@@ -291,8 +312,7 @@ static size_t autotune_bytes(qcoll_plan plan, int64_t batch, size_t ws_bytes) {
   qcoll::Plan p = plan->p;  // copy: only schedule/chunk are varied
   size_t mx = 0;
   for (int sch : {1, onchip_candidate(p)})
-    for (int ck : tune_chunks(batch)) {
-      if (sch < 0) continue;
+    for (int ck : sch < 0 ? std::vector<int>() : tune_chunks(p, sch, batch, ws_bytes)) {
       p.schedule = sch;
       p.chunk = ck;
       mx = std::max(mx, qcoll::make_layout(p, batch, 0, 0, ws_bytes).total);
@@ -368,8 +388,7 @@ qcoll_status qcoll_autotune(qcoll_plan plan, int64_t batch, const double *f, dou
   qcoll_timing_enable(0);
   qcoll_status rc = QCOLL_OK;
   for (int sch : {onchip_candidate(p), 1})
-    for (int ck : tune_chunks(batch)) {
-      if (sch < 0) continue;
+    for (int ck : sch < 0 ? std::vector<int>() : tune_chunks(p, sch, batch, ws_bytes)) {
       p.schedule = sch;
       p.chunk = ck;
       const qcoll::Layout lay = qcoll::make_layout(p, batch, 0, 0, ws_bytes);

@@ -82,6 +82,8 @@ struct Layout {
 
 // chunk > 0 overrides the plan's items per eval chunk (op 0 and 2); ws_bytes:
 // the workspace at hand (optional parts are left out where they do not fit)
+long eval_chunk(const Plan &p);
+long least_chunk(const Plan &p, int op);
 Layout make_layout(const Plan &p, int64_t batch, int op, long chunk = 0, size_t ws_bytes = ~size_t(0));
 // the on-chip gain loop of nbp pairs is faster as one workgroup per term
 bool split_terms(const Plan &p, long nbp);

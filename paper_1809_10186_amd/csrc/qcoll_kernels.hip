@@ -778,19 +778,21 @@ struct OpLowRankC {
   }
 };
 
-// The bilinear gain loop of nbp pairs on chip: the same bits as the two passes,
-// whose time grows with the pairs, while a workgroup's is the same until the
-// chip is full.  Whole calls, on chip against two passes, M = 12: 32^3 (two
-// workgroups per pair) 64 pairs about 0.28 / 0.26 ms, 128 0.29 / 0.45, 1024
-// 1.8 / 3.0; 24^3 128 pairs 0.31 / 0.24, 256 0.37 / 0.42, 1024 1.31 / 1.50
-// (M = 6: 256 pairs 0.23 / 0.22, 512 level); 16^3 128 pairs 115 / 83 us, 256
-// 120 / 125, 1024 204 / 383; 12^3 128 pairs 90 / 73 us, 256 92 / 107; 8^3 128
-// pairs 52 / 48 us, 256 53 / 69.
-static bool use_gain_bil(const Plan &p, long nbp) {
-  if (!use_fused_gain(p)) return false;
-  if (p.N == 32) return nbp > 64;
-  if (p.N == 24) return nbp * p.M >= 3072;
-  return nbp >= 256;
+// How many of nbp pairs, from the front, go through the bilinear gain loop on
+// chip; the rest takes the two passes, with the same bits.  The passes' time
+// grows with the pairs; the chip's with every full set of workgroups, 256 pairs
+// at 24^3 (a tile of 112 KiB each) and 128 at 32^3 (two workgroups a pair), so a
+// last set goes there only if it is full enough.  Whole calls, M = 12, on chip
+// against two passes: 32^3 64 pairs about 0.28 / 0.25 ms, 128 0.29 / 0.44, 1024
+// 1.97 / 3.19; 24^3 160 pairs level at 0.29, 192 0.29 / 0.31, 256 0.29 / 0.42,
+// 1024 1.04 / 1.60; 16^3 128 pairs 115 / 75 us, 256 107 / 119, 512 119 / 205;
+// 12^3 256 80 / 100, 8^3 256 45 / 63 (128 pairs 52 / 43).
+static long gain_bil_pairs(const Plan &p, long nbp) {
+  if (!use_fused_gain(p)) return 0;
+  if (p.N < 24) return nbp >= 256 ? nbp : 0;
+  const long set = p.N == 32 ? 128 : 256, least = p.N == 32 ? 65 : 176;
+  const long r = nbp % set;
+  return r >= least ? nbp : nbp - r;
 }
 
 // ----------------------------------------------------------------------------
@@ -839,11 +841,16 @@ struct Engine {
                                   long pc, hipStream_t st) {
     const long nbp = nb * p.N_rho;
     const T scale = T(1.0 / double(n3));
+    long on = 0;   // the pairs in front that stay on chip
     if constexpr (std::is_same<T, float>::value) {
       // on chip: scratch in Yf (pc * M volumes)
-      if (use_gain_bil(p, nbp)) return launch_gain_bil(p, Hf, Hg, A, Yf, pc * p.M, nbp, st);
+      on = gain_bil_pairs(p, nbp);
+      if (on > 0) {
+        const qcoll_status s = launch_gain_bil(p, Hf, Hg, A, Yf, pc * p.M, on, st);
+        if (s != QCOLL_OK) return s;
+      }
     }
-    for (long bp0 = 0; bp0 < nbp; bp0 += pc) {
+    for (long bp0 = on; bp0 < nbp; bp0 += pc) {
       const long cnt = (nbp - bp0 < pc) ? (nbp - bp0) : pc;
       qcoll_status s;
       SrcShift<T, N> sf{Hf, reinterpret_cast<const C<T> *>(p.phase), bp0, p.M, p.N_rho, scale};
@@ -1087,7 +1094,8 @@ bool use_fused_gain(const Plan &p) {
 // (measured), slots the workgroups the chip holds, wgs those of a pair, u a
 // volume's way through memory at the 7 TB/s that these cache-sized passes reach.
 // Measured, whole call of one item with N_rho = 16 and M = 12, one workgroup per
-// pair against per term: FP32 12^3 42 -> 28 us, 16^3 52 -> 33, 24^3 124 -> 61,
+// pair against per term: FP32 12^3 42 -> 28 us, 16^3 52 -> 33, 24^3 93 -> 53
+// (four items 94 -> 78, and level at six),
 // 32^3 156 -> 74 (two items 158 -> 95, three 159 -> 121, and level at four);
 // FP64 16^3 107 -> 54, 32^3 212 -> 121.  At 8^3 the launches cost what it gains.
 bool split_terms(const Plan &p, long nbp) {
@@ -1099,7 +1107,7 @@ bool split_terms(const Plan &p, long nbp) {
     case 16: t = dp ? 6.5 : 2.5; slots = dp ? 2048 : 1024; wgs = dp ? 4.0 : 1.0; break;
     case 24:
       if (dp) return false;
-      t = 7.5; slots = 512;
+      t = 5.2; slots = 256;
       break;
     case 32: t = dp ? 12.0 : 9.5; slots = 256; wgs = dp ? 2.0 : 1.0; break;
     default: return false;
@@ -1114,6 +1122,31 @@ bool split_terms(const Plan &p, long nbp) {
 // of every pair of 16 items fill 256 CUs twice; more only adds volumes
 constexpr long kTermItems = 16;
 
+// Items per chunk unless the caller sets it.  Small grids need many items to
+// fill the chip, and a launch costs the same few microseconds for any number:
+// M = 12, N_rho = 5, FP32, 64 items a chunk against this many, 2048 items at 8^3
+// 844 -> 90 us, 1024 at 12^3 686 -> 170 and at 16^3 878 -> 350, 512 at 24^3 1431 ->
+// 895, 256 at 32^3 1310 -> 879 (FP64 1782 -> 1124, 1566 -> 1176, 1399 -> 884, 2218
+// -> 1920, 2169 -> 1855).  Above 32^3 64 items fill every launch.
+long eval_chunk(const Plan &p) {
+  return p.N <= 8 ? 2048 : (p.N <= 12 ? 1024 : (p.N <= 16 ? 512 : (p.N <= 32 ? 256 : 64)));
+}
+
+// The same for the vjp: the fused adjoint has no sub-chunks; the two-pass adjoint
+// keeps every term's volumes (FP64, M = 12, N_rho = 8, against 32 items: 1024 at
+// 8^3 3991 -> 892 us, 512 at 12^3 3291 -> 1458, 256 at 16^3 2347 -> 1502 and at 24^3
+// 6522 -> 5309; VSS 128 at 32^3 FP64 7659 -> 7525, FP32 4095 -> 3741).
+static long vjp_chunk(const Plan &p) {
+  if (use_fused_adjoint(p)) return eval_chunk(p);
+  return p.N <= 16 ? 256 : (p.N <= 24 ? 128 : (p.N <= 32 ? 64 : 32));
+}
+
+// The chunk that a workspace too small for the default one is tried with: a
+// workspace sized for this many items serves any batch.
+long least_chunk(const Plan &p, int op) {
+  return op == 1 ? (use_fused_adjoint(p) ? 256 : (use_adjoint_terms64(p) ? 64 : 32)) : 64;
+}
+
 Layout make_layout(const Plan &p, int64_t batch, int op, long chunk, size_t ws_bytes) {
   Layout l;
   const size_t es = (p.precision == QCOLL_FP32) ? sizeof(float) : sizeof(double);
@@ -1126,10 +1159,8 @@ Layout make_layout(const Plan &p, int64_t batch, int op, long chunk, size_t ws_b
     // group of slabs of the sub-chunk's items, so the sub-chunk must hold enough
     // items to fill the GPU (32 items at N = 32 in FP64: 1024 workgroups); Y is
     // capped at 4 GiB.
-    // The fused adjoint has no sub-chunks: its chunks hold up to 256 items
-    // (fewer, larger launches of the small passes around it).
     const bool t64 = use_adjoint_terms64(p);
-    const long cap = use_fused_adjoint(p) ? 256 : (t64 ? 64 : 32);
+    const long cap = chunk > 0 ? chunk : vjp_chunk(p);
     l.bc = batch < cap ? (batch > 0 ? batch : 1) : cap;
     // (VSS kernels add the paired h_pq volumes, ceil(M/2) complex volumes per pair)
     const size_t per_item_y = size_t(p.N_rho) * p.M * n3 * 2 * es;
@@ -1169,9 +1200,12 @@ Layout make_layout(const Plan &p, int64_t batch, int op, long chunk, size_t ws_b
     l.off_yh = o; o += al(size_t(l.pc) * per_item_yh);
     l.off_zp = o; o += t64 ? al(size_t(kAccParts) * l.bc * n3 * 2 * sizeof(double)) : 0;
     l.total = o;
+    // a workspace sized for fewer items than the default chunk
+    if (chunk == 0 && l.total > ws_bytes && l.bc > least_chunk(p, op))
+      return make_layout(p, batch, op, least_chunk(p, op), ws_bytes);
     return l;
   }
-  const long cmax = chunk > 0 ? chunk : (p.chunk > 0 ? p.chunk : 64);
+  const long cmax = chunk > 0 ? chunk : (p.chunk > 0 ? p.chunk : eval_chunk(p));
   l.bc = batch < cmax ? (batch > 0 ? batch : 1) : cmax;
   const bool bil = (op == 2);
   // two-pass hot loop: (item, node) pairs per launch such that the launch's
@@ -1184,6 +1218,12 @@ Layout make_layout(const Plan &p, int64_t batch, int op, long chunk, size_t ws_b
     const size_t per_pair = size_t(p.M) * n3 * 2 * es * (lit ? 2 : 1);
     long pc = long((size_t(192) << 20) / per_pair);
     l.pc = pc < 8 ? 8 : (pc > 128 ? 128 : pc);
+    // small grids: more pairs, until the volumes of a launch pass half of the
+    // cache (FP64, M = 12, N_rho = 8, 2048 items at 8^3 1774 -> 639 us, 1024 at
+    // 12^3 1911 -> 1119; with two volumes per term 64 MiB each: 3417 -> 1297 us,
+    // 128 MiB 1419)
+    const long more = long((size_t(bil || lit ? 64 : 128) << 20) / per_pair);
+    if (l.pc < more) l.pc = more;
   }
   if (l.pc > l.bc * p.N_rho) l.pc = l.bc * p.N_rho;
   const bool t64 = use_vss_terms64(p) && !bil;
@@ -1223,6 +1263,9 @@ Layout make_layout(const Plan &p, int64_t batch, int op, long chunk, size_t ws_b
     l.off_h64g = o; o += al(size_t(l.bc) * n3 * 2 * sizeof(double));
     l.off_yg = o; o += al(size_t(l.pc) * p.M * n3 * 2 * es);
   }
+  // a workspace sized for fewer items than the default chunk
+  if (chunk == 0 && p.chunk == 0 && o > ws_bytes && l.bc > least_chunk(p, op))
+    return make_layout(p, batch, op, least_chunk(p, op), ws_bytes);
   if (!bil && split_terms(p, l.bc * p.N_rho)) {
     const size_t u = al(size_t(l.bc) * p.N_rho * (p.M - 1) * n3 * 2 * es);
     // a workspace sized for another batch may not hold them: the loop then runs

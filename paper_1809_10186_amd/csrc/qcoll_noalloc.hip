@@ -60,9 +60,9 @@ extern "C" qcoll_status qcoll_eval_noalloc(qcoll_plan plan, int64_t batch, const
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return nfail(QCOLL_EDEVICE, "hipGetDevice failed");
   if (dev != p.device) return nfail(QCOLL_EINVAL, "current device differs from the plan's device");
-  // items per chunk: the plan's chunk (default 64), reduced until one chunk's
+  // items per chunk: the plan's chunk, reduced until one chunk's
   // workspace fits the array (the workspace grows with the chunk)
-  const long want = std::min<long>(batch, p.chunk > 0 ? p.chunk : 64);
+  const long want = std::min<long>(batch, p.chunk > 0 ? p.chunk : qcoll::eval_chunk(p));
   if (qcoll::make_layout(p, batch, 0, 1, 0).total > kScratchBytes)
     return nfail(QCOLL_EWORKSPACE, "one item of this plan needs " +
                                        std::to_string(qcoll::make_layout(p, batch, 0, 1, 0).total) +
