@@ -99,91 +99,9 @@ struct SlabTile {
 };
 
 template <typename T, int N, int SIGN, class Src, class Dst>
-__device__ __forceinline__ void slab_body(SlabTile<T, N> &tile, const Src &src, const Dst &dst, long nslab) {
-  constexpr int SPB = slab_spb<T, N>();
-  constexpr bool SPLIT = slab_split<T, N>();
-  const int s = int(threadIdx.x) / N, c = int(threadIdx.x) % N;
-  const long g = long(blockIdx.x) * SPB + s;
-  const long gl = g < nslab ? g : nslab - 1;
-  T xr[N], xi[N];
-  if constexpr (grouped_loads<Src>::value) {
-    constexpr int LG = (N % 16 == 0) ? 16 : ((N % 8 == 0) ? 8 : 4);
-    static_for<0, N / LG>([&](auto gg) {
-      constexpr int r0 = decltype(gg)::value * LG;
-      decltype(src.raw(gl, 0, c)) v[LG];
-      static_for<0, LG>([&](auto ii) { v[decltype(ii)::value] = src.raw(gl, r0 + decltype(ii)::value, c); });
-      __builtin_amdgcn_sched_barrier(0);
-      static_for<0, LG>([&](auto ii) {
-        xr[r0 + decltype(ii)::value] = T(v[decltype(ii)::value].re);
-        xi[r0 + decltype(ii)::value] = T(v[decltype(ii)::value].im);
-      });
-    });
-  } else {
-    static_for<0, N>([&](auto r) {
-      const C<T> v = src(gl, decltype(r)::value, c);
-      xr[decltype(r)::value] = v.re;
-      xi[decltype(r)::value] = v.im;
-    });
-  }
-  fft_reg<N, SIGN, T>(xr, xi);
-  if constexpr (SPLIT) {
-    // one tile, one component at a time: column -> row, row FFT, row -> column
-    auto &sb = tile.v[0];
-    const int row = c;
-    auto to_rows = [&](T *x) {
-      static_for<0, N>([&](auto r) { sb[s][decltype(r)::value][c] = x[decltype(r)::value]; });
-      __syncthreads();
-      static_for<0, N>([&](auto k) { x[decltype(k)::value] = sb[s][row][decltype(k)::value]; });
-      __syncthreads();
-    };
-    auto to_cols = [&](T *x) {
-      static_for<0, N>([&](auto k) { sb[s][row][decltype(k)::value] = x[decltype(k)::value]; });
-      __syncthreads();
-      static_for<0, N>([&](auto r) { x[decltype(r)::value] = sb[s][decltype(r)::value][c]; });
-      __syncthreads();
-    };
-    to_rows(xr);
-    to_rows(xi);
-    fft_reg<N, SIGN, T>(xr, xi);
-    to_cols(xr);
-    to_cols(xi);
-    if (g < nslab) {
-      static_for<0, N>([&](auto r) {
-        dst(g, decltype(r)::value, c, C<T>{xr[decltype(r)::value], xi[decltype(r)::value]});
-      });
-    }
-    return;
-  } else {
-    auto &sre = tile.v[0];
-    auto &sim = tile.v[1];
-    static_for<0, N>([&](auto r) {
-      sre[s][decltype(r)::value][c] = xr[decltype(r)::value];
-      sim[s][decltype(r)::value][c] = xi[decltype(r)::value];
-    });
-    __syncthreads();
-    const int row = c;
-    static_for<0, N>([&](auto k) {
-      xr[decltype(k)::value] = sre[s][row][decltype(k)::value];
-      xi[decltype(k)::value] = sim[s][row][decltype(k)::value];
-    });
-    fft_reg<N, SIGN, T>(xr, xi);
-    static_for<0, N>([&](auto k) {
-      sre[s][row][decltype(k)::value] = xr[decltype(k)::value];
-      sim[s][row][decltype(k)::value] = xi[decltype(k)::value];
-    });
-    __syncthreads();
-    if (g < nslab) {
-      static_for<0, N>([&](auto r) {
-        dst(g, decltype(r)::value, c, C<T>{sre[s][decltype(r)::value][c], sim[s][decltype(r)::value][c]});
-      });
-    }
-  }
-}
-
-template <typename T, int N, int SIGN, class Src, class Dst>
 __global__ __launch_bounds__(256) void k_slab(Src src, Dst dst, long nslab) {
   __shared__ SlabTile<T, N> tile;
-  slab_body<T, N, SIGN>(tile, src, dst, nslab);
+#include "qcoll_slab_body.hpp"
 }
 
 // two slab passes of the same size as one launch (blockIdx.y): the gain and the
@@ -191,8 +109,17 @@ __global__ __launch_bounds__(256) void k_slab(Src src, Dst dst, long nslab) {
 template <typename T, int N, int SIGN, class S0, class D0, class S1, class D1>
 __global__ __launch_bounds__(256) void k_slab2(S0 s0, D0 d0, S1 s1, D1 d1, long nslab) {
   __shared__ SlabTile<T, N> tile;
-  if (blockIdx.y == 0) slab_body<T, N, SIGN>(tile, s0, d0, nslab);
-  else slab_body<T, N, SIGN>(tile, s1, d1, nslab);
+  if (blockIdx.y == 0) {
+    using Src = S0;
+    const S0 &src = s0;
+    const D0 &dst = d0;
+#include "qcoll_slab_body.hpp"
+  } else {
+    using Src = S1;
+    const S1 &src = s1;
+    const D1 &dst = d1;
+#include "qcoll_slab_body.hpp"
+  }
 }
 
 // generic pencil kernel: Op(pencil_group, r) with r = j2*N + j3
