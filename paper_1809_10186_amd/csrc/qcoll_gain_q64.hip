@@ -44,7 +44,7 @@ struct Q64Geom {
   // the stage-2 transpose stays inside a wave when the N/4 lanes of a k1 do
   static constexpr bool WAVE2 = (64 % N4 == 0);
   // rows of stage-1 loads in flight (4 pencils each)
-  static constexpr int KG = 4;
+  static constexpr int KG = 4;   // rows of H loaded together (a row at a time 47.9 us a call of one 16^3 item, 45.6 so)
 };
 
 // stage 1 for residue class G: v[m N/4 + u] = X_m[4u + G], X_m the inverse

@@ -14,7 +14,9 @@
 //   VSS      Z = sum (alpha_q - i alpha_q')(k) P(k)     (Re ifft3[Z]: alpha is
 //            even and real, so C_q t_q + C_q' t_q' is the real part).
 // k_terms_c2 is bound like k_gain_c2 (VALU issue, LDS and L2 reads in turn)
-// with half of its transforms more, k_acc_terms by its reads.
+// with half of its transforms more, k_acc_terms by its reads.  N_rho 16, M 12,
+// through the projection: VJP of 37 items 4.00 ms in passes, 2.26 ms so (a launch
+// of 16 items: terms 440 us, sums 251 us); VSS of 45 items 3.08 -> 2.18 ms.
 #include <hip/hip_runtime.h>
 
 #include "qcoll_c2.hpp"
