@@ -234,11 +234,11 @@ struct OpLowRank {
   const T *V;
   C<double> *TA;
   int npair;
-  __device__ void operator()(long b, int r) const {
+  // the sum over the pairs [s0, s1)
+  __device__ __forceinline__ void sum(long b, int r, int s0, int s1, T *tr, T *ti) const {
     constexpr long n2 = long(N) * N, n3 = n2 * N;
-    T tr[N], ti[N];
     static_for<0, N>([&](auto k) { tr[decltype(k)::value] = T(0); ti[decltype(k)::value] = T(0); });
-    for (int s = 0; s < npair; ++s) {
+    for (int s = s0; s < s1; ++s) {
       const C<double> *w = W + (b * npair + s) * n3 + r;
       T xr[N], xi[N];
       static_for<0, N>([&](auto k) {
@@ -279,12 +279,82 @@ struct OpLowRank {
         });
       });
     }
+  }
+  __device__ void operator()(long b, int r) const {
+    constexpr long n2 = long(N) * N, n3 = n2 * N;
+    T tr[N], ti[N];
+    sum(b, r, 0, npair, tr, ti);
     C<double> *o = TA + b * n3 + r;
     static_for<0, N>([&](auto k) {
       o[decltype(k)::value * n2] = C<double>{double(tr[decltype(k)::value]), double(ti[decltype(k)::value])};
     });
   }
 };
+
+// Grids up to 32^3: the pairs in four fixed parts, added in order.  For few items
+// (16 waves for one of 32^3) the pass is a chain of load and transform per pair, so
+// k_low_rank_parts gives each part a wave of a workgroup of 64 pencils; for many it
+// is bound by the reads of W and loses by that workgroup's reduction, so
+// k_low_rank_chain takes the parts in turn, the total in LDS (the registers hold one
+// part's sum and a pencil).  The same bits.  16 nodes (8 pairs) at 32^3, 8 else, one
+// chain without parts before: 1 item at 32^3 36 -> 16 us, 24^3 15 -> 9, 16^3 11 -> 7.4,
+// 1024 at 12^3 36 -> 27; in turn 192 at 32^3 202 -> 218 us, 100 at 24^3 26 -> 27, 512 at
+// 16^3 39 -> 38 (side by side 247, 29 and 44).
+constexpr int kLowRankParts = 4;
+
+template <int N>
+__global__ __launch_bounds__(64 * kLowRankParts) void k_low_rank_parts(OpLowRank<double, N> op, long npencil) {
+  constexpr long n2 = long(N) * N, n3 = n2 * N;
+  __shared__ double sums[kLowRankParts - 1][N][64];
+  const int lane = int(threadIdx.x) % 64, part = int(threadIdx.x) / 64;
+  const long pen = long(blockIdx.x) * 64 + lane;
+  const long pl = pen < npencil ? pen : npencil - 1;   // lanes past the end load it and store nothing
+  const long b = pl / n2;
+  const int r = int(pl % n2);
+  double tr[N], ti[N];
+  op.sum(b, r, (part * op.npair) / kLowRankParts, ((part + 1) * op.npair) / kLowRankParts, tr, ti);
+  auto add = [&](double *t) {
+    if (part > 0) static_for<0, N>([&](auto k) { sums[part - 1][decltype(k)::value][lane] = t[decltype(k)::value]; });
+    __syncthreads();
+    if (part == 0) {
+#pragma unroll
+      for (int i = 0; i < kLowRankParts - 1; ++i)
+        static_for<0, N>([&](auto k) { t[decltype(k)::value] += sums[i][decltype(k)::value][lane]; });
+    }
+  };
+  add(tr);
+  __syncthreads();
+  add(ti);
+  if (part == 0 && pen < npencil) {
+    C<double> *o = op.TA + b * n3 + r;
+    static_for<0, N>([&](auto k) { o[decltype(k)::value * n2] = C<double>{tr[decltype(k)::value], ti[decltype(k)::value]}; });
+  }
+}
+
+template <int N>
+__global__ __launch_bounds__(64) void k_low_rank_chain(OpLowRank<double, N> op, long npencil) {
+  constexpr long n2 = long(N) * N, n3 = n2 * N;
+  __shared__ double total[2][N][64];   // a column per lane
+  const int lane = int(threadIdx.x);
+  const long pen = long(blockIdx.x) * 64 + lane;
+  if (pen >= npencil) return;
+  const long b = pen / n2;
+  const int r = int(pen % n2);
+  C<double> *o = op.TA + b * n3 + r;
+  for (int part = 0; part < kLowRankParts; ++part) {
+    double tr[N], ti[N];
+    op.sum(b, r, (part * op.npair) / kLowRankParts, ((part + 1) * op.npair) / kLowRankParts, tr, ti);
+    if (part > 0) static_for<0, N>([&](auto k) {
+      tr[decltype(k)::value] = total[0][decltype(k)::value][lane] + tr[decltype(k)::value];
+      ti[decltype(k)::value] = total[1][decltype(k)::value][lane] + ti[decltype(k)::value];
+    });
+    if (part < kLowRankParts - 1) static_for<0, N>([&](auto k) {
+      total[0][decltype(k)::value][lane] = tr[decltype(k)::value];
+      total[1][decltype(k)::value][lane] = ti[decltype(k)::value];
+    });
+    else static_for<0, N>([&](auto k) { o[decltype(k)::value * n2] = C<double>{tr[decltype(k)::value], ti[decltype(k)::value]}; });
+  }
+}
 
 // fused schedule: gain spectrum = sum over the radial nodes of the per-node
 // half spectra W[b][p] (n_in float4 each) into the item's spectrum (n_out
@@ -1071,7 +1141,20 @@ struct Engine {
                SrcPair<T, N, double>{Bsrc, S, np}, DstCplx<double, N>{Wd}, nb * np * N, st, "low-rank slab")))
         return s;
       OpLowRank<double, N> lr{Wd, p.v64(), TA, np};
-      if ((s = pencil(lr, nb * N * N, st, "low-rank pencil"))) return s;
+      if constexpr (N <= 32) {
+        TimedLaunch tl("low-rank pencil", st);
+        // parts side by side while their workgroups are at most one (32^3: 16 items
+        // 22 us against 36 in turn, 64 95 against 74) or two a CU (24^3: 30 items 14 /
+        // 17, 100 29 / 27; 16^3: 128 items level at 13); below 16^3 always
+        const unsigned wgs = nblk(nb * N * N, 64);
+        if (N < 16 || wgs <= (N == 32 ? 256u : 512u))
+          hipLaunchKernelGGL((k_low_rank_parts<N>), dim3(wgs), dim3(64 * kLowRankParts), 0, st, lr, nb * N * N);
+        else
+          hipLaunchKernelGGL((k_low_rank_chain<N>), dim3(wgs), dim3(64), 0, st, lr, nb * N * N);
+        QC_LAUNCH_CHECK("low-rank pencil");
+      } else {
+        if ((s = pencil(lr, nb * N * N, st, "low-rank pencil"))) return s;
+      }
       if ((s = Passes<double, N>::template slab2<+1>(SrcCplx<double, N>{TA}, DstCplx<double, N>{TA},
                SrcLoss<N>{g ? H64g : H64, reinterpret_cast<const double *>(p.lam)}, DstCplx<double, N>{LH},
                nb * N, st, "inverse slabs")))

@@ -89,3 +89,16 @@ def test_group_in_a_workspace_sized_for_fewer_items():
         assert torch.equal(Q, want)
     assert L.qcoll_group_eval(whole._h, qc.Group._arr([f]), qc.Group._arr([Q]), 0, qc._ptr(ws),
                               ctypes.c_size_t(256), None, 0) != 0
+
+
+@pytest.mark.parametrize("N,N_rho,items,few", [(8, 9, 20, 3), (12, 9, 20, 3), (16, 9, 131, 16), (16, 3, 131, 16),
+                                               (24, 11, 60, 8), (32, 9, 18, 5), (32, 2, 18, 5)])
+def test_low_rank_parts_in_turn_and_side_by_side(N, N_rho, items, few):
+    """The low-rank pass sums its pairs in the same four parts at any number of items."""
+    print(f"case N={N} N_rho={N_rho} items={items}", flush=True)
+    plan = qc.Plan(N, 6.0, N_rho, sphere=W.sphere_rule(6), omega=0.81)
+    f = _fields(items, N, 9)
+    a = plan.eval(f)
+    plan.set_chunk(few)
+    assert torch.equal(a, plan.eval(f))
+    assert torch.equal(a[:1], plan.eval(f[:1].contiguous()))
