@@ -158,87 +158,103 @@ __global__ __launch_bounds__(C2Geom<N>::NL) void k_terms_c2(const cplx<double> *
   }
 }
 
-// Z part: one lane per pencil (k2, k3) of an item and per parity G of k1 (the
-// transform's other outputs are dropped at compile time, which leaves room for
-// the sums beside the pencil), over the volumes of the nodes
-// [part Nr / kAccParts, (part + 1) Nr / kAccParts): a fixed split, so that an
-// item's result does not depend on the launch.
-template <int N, int MODE, int G>
-__device__ __forceinline__ void acc_terms(const cplx<double> *__restrict__ Y, const cplx<double> *__restrict__ phase,
-                                          const double *__restrict__ apq, cplx<double> *__restrict__ Z, long bl,
-                                          int pen, int p0, int p1, int M, int Nr) {
-  constexpr int n2 = N * N, HN = N / 2;
-  constexpr long n3 = long(n2) * N, nh = long(HN + 1) * n2;
-  const int MV = MODE == 0 ? M : (M + 1) / 2;
-  const int k2 = pen / N, k3 = pen % N;
-  const int refl = ((N - k2) % N) * N + (N - k3) % N;
-  double ar[HN], ai[HN];
-  static_for<0, HN>([&](auto i) { ar[decltype(i)::value] = 0.0; ai[decltype(i)::value] = 0.0; });
-  // k1 of sum i: the outputs of column k = G mod 2 of the decimated transform
-  constexpr auto k1_of = [](int i) { return G + 2 * (i / 4) + (N / 4) * (i % 4); };
-  for (int p = p0; p < p1; ++p) {
-    for (int v = 0; v < MV; ++v) {
-      __syncthreads();   // both parities read a volume together (the second from cache)
-      const __amdgpu_buffer_rsrc_t yr =
-          make_rsrc(Y + ((bl * Nr + p) * MV + v) * n3, unsigned(n3 * sizeof(cplx<double>)));
-      double xr[N], xi[N];
-      static_for<0, N>([&](auto j) {
-        const cplx<double> x = load_c64(yr, pen * int(sizeof(cplx<double>)),
-                                        int(decltype(j)::value * n2 * sizeof(cplx<double>)));
-        xr[decltype(j)::value] = x.re;
-        xi[decltype(j)::value] = x.im;
-      });
-      if constexpr (MODE == 0) {
-        const cplx<double> *ph = phase + size_t(p * M + v) * 3 * N;
-        const cplx<double> b2 = ph[N + k2], b3 = ph[2 * N + k3];
-        const double x = b2.re * b3.re - b2.im * b3.im, y = b2.re * b3.im + b2.im * b3.re;
-        const double P = x + y, Q = x - y;
-        fft_reg<N, -1, double>(xr, xi);
-        static_for<0, HN>([&](auto i) {
-          constexpr int ii = decltype(i)::value, k1 = k1_of(ii);
-          const cplx<double> b1 = ph[k1];
-          const double c = b1.re * P + b1.im * Q;
-          ar[ii] += c * xr[k1];
-          ai[ii] += c * xi[k1];
-        });
-      } else {
-        // alpha_pq on the planes k1 <= N/2; plane k1 > N/2 at the reflected index
-        const double *a0 = apq + (size_t(p) * M + 2 * v) * nh;
-        const bool two = 2 * v + 1 < M;
-        const double *a1 = two ? a0 + nh : a0;
-        fft_reg<N, -1, double>(xr, xi);
-        static_for<0, HN>([&](auto i) {
-          constexpr int ii = decltype(i)::value, k1 = k1_of(ii);
-          const int o = k1 <= HN ? k1 * n2 + pen : (N - k1) * n2 + refl;
-          const double w0 = a0[o], r1 = a1[o], w1 = two ? r1 : 0.0;
-          // (w0 - i w1)(x + i y)
-          ar[ii] += w0 * xr[k1] + w1 * xi[k1];
-          ai[ii] += w0 * xi[k1] - w1 * xr[k1];
-        });
-      }
-    }
-  }
-  cplx<double> *z = Z + bl * n3 + pen;
-  static_for<0, HN>([&](auto i) {
-    z[k1_of(decltype(i)::value) * n2] = cplx<double>{ar[decltype(i)::value], ai[decltype(i)::value]};
-  });
+// k1 of sum i of parity G: the outputs of column k = G mod 2 of the decimated
+// transform (the others are dropped at compile time, which leaves room for the
+// sums beside the pencil)
+template <int N, int G>
+constexpr int acc_k1(int i) {
+  return G + 2 * (i / 4) + (N / 4) * (i % 4);
 }
 
+// the pencil pen of volume y into the sums of parity G.  Each parity loads for
+// itself: with the loads ahead of the branch 18 (MODE 0) and 43 (MODE 1)
+// registers spill, none so.
+template <int N, int MODE, int G>
+__device__ __forceinline__ void acc_term(const cplx<double> *__restrict__ y, const cplx<double> *__restrict__ phase,
+                                         const double *__restrict__ apq, int p, int v, int M, int pen, double *ar,
+                                         double *ai) {
+  constexpr int n2 = N * N, HN = N / 2;
+  constexpr long n3 = long(n2) * N, nh = long(HN + 1) * n2;
+  const int k2 = pen / N, k3 = pen % N;
+  const __amdgpu_buffer_rsrc_t yr = make_rsrc(y, unsigned(n3 * sizeof(cplx<double>)));
+  double xr[N], xi[N];
+  auto load = [&] {
+    static_for<0, N>([&](auto j) {
+      const cplx<double> x = load_c64(yr, pen * int(sizeof(cplx<double>)),
+                                      int(decltype(j)::value * n2 * sizeof(cplx<double>)));
+      xr[decltype(j)::value] = x.re;
+      xi[decltype(j)::value] = x.im;
+    });
+  };
+  if constexpr (MODE == 0) {
+    const cplx<double> *ph = phase + size_t(p * M + v) * 3 * N;
+    load();   // all of it in flight before the factors are asked for
+    __builtin_amdgcn_sched_barrier(0);
+    const cplx<double> b2 = ph[N + k2], b3 = ph[2 * N + k3];
+    const double cr = b2.re * b3.re - b2.im * b3.im, ci = b2.re * b3.im + b2.im * b3.re;
+    const double P = cr + ci, Q = cr - ci;
+    fft_reg<N, -1, double>(xr, xi);
+    static_for<0, HN>([&](auto i) {
+      constexpr int ii = decltype(i)::value, k1 = acc_k1<N, G>(ii);
+      const cplx<double> b1 = ph[k1];
+      const double c = b1.re * P + b1.im * Q;
+      ar[ii] += c * xr[k1];
+      ai[ii] += c * xi[k1];
+    });
+  } else {
+    // alpha_pq on the planes k1 <= N/2; plane k1 > N/2 at the reflected index
+    const int refl = ((N - k2) % N) * N + (N - k3) % N;
+    const double *a0 = apq + (size_t(p) * M + 2 * v) * nh;
+    const bool two = 2 * v + 1 < M;
+    const double *a1 = two ? a0 + nh : a0;
+    load();
+    fft_reg<N, -1, double>(xr, xi);
+    static_for<0, HN>([&](auto i) {
+      constexpr int ii = decltype(i)::value, k1 = acc_k1<N, G>(ii);
+      const int o = k1 <= HN ? k1 * n2 + pen : (N - k1) * n2 + refl;
+      const double w0 = a0[o], r1 = a1[o], w1 = two ? r1 : 0.0;
+      // (w0 - i w1)(x + i y)
+      ar[ii] += w0 * xr[k1] + w1 * xi[k1];
+      ai[ii] += w0 * xi[k1] - w1 * xr[k1];
+    });
+  }
+}
+
+// Z part: one lane per pencil (k2, k3) of an item and per parity of k1, over the
+// volumes of the nodes [part Nr / kAccParts, (part + 1) Nr / kAccParts): a fixed
+// split, so that an item's result does not depend on the launch.
 template <int N, int MODE>
 __global__ __launch_bounds__(256, 2) void k_acc_terms(const cplx<double> *__restrict__ Y,
                                                       const cplx<double> *__restrict__ phase,
                                                       const double *__restrict__ apq, cplx<double> *__restrict__ Z,
                                                       long part_stride, int M, int Nr) {
+  constexpr int n2 = N * N, HN = N / 2;
+  constexpr long n3 = long(n2) * N;
   // a workgroup: 128 pencils, waves 0 and 1 their even k1, waves 2 and 3 the odd
-  constexpr int GP = N * N / 128;
+  constexpr int GP = n2 / 128;
   const long bl = blockIdx.x / GP;
-  const int wave = int(threadIdx.x) / 64;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / 64);
   const int pen = int(blockIdx.x % GP) * 128 + (wave % 2) * 64 + int(threadIdx.x) % 64;
   const int part = int(blockIdx.y);
   const int p0 = part * Nr / kAccParts, p1 = (part + 1) * Nr / kAccParts;
-  cplx<double> *z = Z + part * part_stride;
-  if (wave < 2) acc_terms<N, MODE, 0>(Y, phase, apq, z, bl, pen, p0, p1, M, Nr);
-  else acc_terms<N, MODE, 1>(Y, phase, apq, z, bl, pen, p0, p1, M, Nr);
+  const int MV = MODE == 0 ? M : (M + 1) / 2;
+  double ar[HN], ai[HN];
+  static_for<0, HN>([&](auto i) { ar[decltype(i)::value] = 0.0; ai[decltype(i)::value] = 0.0; });
+  for (int p = p0; p < p1; ++p) {
+    for (int v = 0; v < MV; ++v) {
+      // both parities read a volume together (the second from cache): one barrier
+      // that all four waves meet, ahead of the branch on the parity
+      __syncthreads();
+      const cplx<double> *y = Y + ((bl * Nr + p) * MV + v) * n3;
+      if (wave < 2) acc_term<N, MODE, 0>(y, phase, apq, p, v, M, pen, ar, ai);
+      else acc_term<N, MODE, 1>(y, phase, apq, p, v, M, pen, ar, ai);
+    }
+  }
+  cplx<double> *z = Z + part * part_stride + bl * n3 + pen;
+  const int g = wave / 2;
+  static_for<0, HN>([&](auto i) {
+    z[(g + acc_k1<N, 0>(decltype(i)::value)) * n2] = cplx<double>{ar[decltype(i)::value], ai[decltype(i)::value]};
+  });
 }
 
 // dwg[pair] = both classes' parts
