@@ -68,6 +68,7 @@ constexpr int kDomSeg = 16;
 struct Layout {
   long bc = 0;          // items per chunk
   long pc = 0;          // eval: (item, radial node) pairs per hot-loop launch; vjp: items per sub-chunk
+  int pn = 0;           // FP64 VSS terms on chip (pc: items): nodes per launch, less than N_rho only with pc = 1
   size_t off_h = 0, off_h64 = 0, off_a = 0, off_b = 0, off_w = 0, off_t = 0, off_l = 0, off_y = 0;
   size_t off_g = 0, off_z = 0, off_hp = 0, off_d = 0, off_pm = 0, off_dp = 0;  // vjp extras
   size_t off_pd = 0;                                    // two-pass vjp: per-pencil omega-gradient parts
@@ -85,6 +86,10 @@ struct Layout {
 long eval_chunk(const Plan &p);
 long least_chunk(const Plan &p, int op);
 Layout make_layout(const Plan &p, int64_t batch, int op, long chunk = 0, size_t ws_bytes = ~size_t(0));
+// the layout of qcoll_eval_noalloc in its array of kScratchBytes; false: one item
+// does not fit (lay.total says what it needs)
+constexpr size_t kScratchBytes = size_t(256) << 20;   // 256 MiB per device
+bool noalloc_layout(const Plan &p, int64_t batch, Layout &lay);
 // the on-chip gain loop of nbp pairs is faster as one workgroup per term
 bool split_terms(const Plan &p, long nbp);
 
@@ -122,15 +127,15 @@ bool use_gain_q64(const Plan &p);
 qcoll_status launch_gain_q64(const Plan &p, const void *H, double *A, void *U, long nbp, hipStream_t st);
 // FP64 term loops on chip with the spectrum of every term's product (N = 32):
 // Z [kAccParts] parts of the items' spectra, part_stride elements apart, their
-// sum in order is the result; Y: pc items' volumes (M a pair, VSS (M + 1) / 2);
-// dots: two values per pair
+// sum in order is the result; Y: pc items' volumes (M a pair, VSS (M + 1) / 2 of pn
+// nodes); dots: two values per pair
 constexpr int kAccParts = 4;
 bool use_adjoint_terms64(const Plan &p);   // unless the two-pass schedule was requested
 bool use_vss_terms64(const Plan &p);       // unless the schedule is two-pass
 qcoll_status launch_adjoint_terms64(const Plan &p, const void *H, const double *Hp, void *Y, void *Z,
                                     long part_stride, double *dots, double *dwg, long nb, long pc, hipStream_t st);
 qcoll_status launch_vss_terms64(const Plan &p, const void *H, void *Y, void *Z, long part_stride, long nb, long pc,
-                                hipStream_t st);
+                                int pn, hipStream_t st);
 // schedule 2 exists for this grid and precision (FP32 fused kernel or FP64 on-chip gain)
 inline bool onchip_schedule_supported(int N, int precision) {
   return fused_gain_supported(N, precision) || gain_q64_supported(N, precision);

@@ -942,7 +942,7 @@ struct Engine {
   // (Hg, H64g, Yg non-null: the bilinear Q(f, g), two-pass in both precisions)
   static qcoll_status eval_vss(const Plan &p, const C<T> *H, const C<double> *H64, T *A, C<T> *Y, C<double> *TA,
                                C<T> *VP, C<double> *Zp, long zstride, C<double> *LH, const double *fb,
-                               double *Qb, long nb, long pc,
+                               double *Qb, long nb, long pc, int pn,
                                hipStream_t st, const double *isc, int K, long b0, const C<T> *Hg = nullptr,
                                const C<double> *H64g = nullptr, C<T> *Yg = nullptr) {
     constexpr int H1 = N / 2 + 1;
@@ -958,7 +958,7 @@ struct Engine {
       // the terms' spectra on chip, then the full-spectrum tail (Z is not Hermitian,
       // the gain is its real part)
       if (use_vss_terms64(p) && !Hg) {
-        if ((s = launch_vss_terms64(p, H, Y, Zp, zstride, nb, pc, st))) return s;
+        if ((s = launch_vss_terms64(p, H, Y, Zp, zstride, nb, pc, pn, st))) return s;
         if ((s = Passes<double, N>::template slab2<+1>(SrcParts<double, N>{Zp, zstride}, DstCplx<double, N>{TA},
                  SrcLoss<N>{H64, reinterpret_cast<const double *>(p.lam)}, DstCplx<double, N>{LH},
                  nb * N, st, "inverse slabs")))
@@ -1084,7 +1084,7 @@ struct Engine {
       if constexpr (N <= 48) {   // VSS kernels: N <= 48 (the plan refuses larger grids)
         if (p.is_vss()) {
           if (g && (s = Passes<double, N>::template forward_to<T>(g + b0 * n3, H64g, Hg, nb, st))) return s;
-          if ((s = eval_vss(p, H, H64, A, Y, TA, VP, reinterpret_cast<C<double> *>(w + lay.off_zp), lay.bc * n3, LH, fb, Q + b0 * n3, nb, lay.pc, st, isc, K, b0,
+          if ((s = eval_vss(p, H, H64, A, Y, TA, VP, reinterpret_cast<C<double> *>(w + lay.off_zp), lay.bc * n3, LH, fb, Q + b0 * n3, nb, lay.pc, lay.pn, st, isc, K, b0,
                             g ? Hg : nullptr, g ? H64g : nullptr, g ? Yg : nullptr)))
             return s;
           continue;
@@ -1310,10 +1310,18 @@ Layout make_layout(const Plan &p, int64_t batch, int op, long chunk, size_t ws_b
   }
   if (l.pc > l.bc * p.N_rho) l.pc = l.bc * p.N_rho;
   const bool t64 = use_vss_terms64(p) && !bil;
-  const size_t per_item_y = size_t(p.N_rho) * ((p.M + 1) / 2) * n3 * 2 * es;
+  const size_t per_node_y = size_t((p.M + 1) / 2) * n3 * 2 * es;
   if (t64) {
-    // items per launch of the on-chip term loop: their volumes within 2 GiB
-    const long pc = long((size_t(2) << 30) / per_item_y);
+    // items per launch of the on-chip term loop, their volumes within 2 GiB; a part
+    // of one item's nodes where its volumes are more, or more than a workspace of
+    // fixed size holds beside the item's seven other volumes (a chunk of one item is
+    // asked for)
+    size_t room = size_t(2) << 30;
+    const size_t rest = 7 * al(size_t(n3) * 2 * es);
+    if (chunk == 1 && ws_bytes < rest + room) room = ws_bytes > rest ? ws_bytes - rest : 0;
+    const long nodes = long(room / per_node_y);
+    l.pn = int(nodes < 1 ? 1 : (nodes > p.N_rho ? p.N_rho : nodes));
+    const long pc = nodes / p.N_rho;
     l.pc = pc < 1 ? 1 : (pc > kTermItems ? kTermItems : pc);
     if (l.pc > l.bc) l.pc = l.bc;
   }
@@ -1333,7 +1341,7 @@ Layout make_layout(const Plan &p, int64_t batch, int op, long chunk, size_t ws_b
   l.off_l = o; o += al(size_t(l.bc) * n3 * 2 * sizeof(double));
   const bool q64 = use_gain_q64(p) && !bil;   // FP64 gain on chip: no per-term volumes
   l.off_y = o;
-  o += (fused || q64) ? 0 : (t64 ? al(size_t(l.pc) * per_item_y) : al(size_t(l.pc) * p.M * n3 * 2 * es));
+  o += (fused || q64) ? 0 : (t64 ? al(size_t(l.pc) * l.pn * per_node_y) : al(size_t(l.pc) * p.M * n3 * 2 * es));
   l.off_zp = o; o += t64 ? al(size_t(kAccParts) * l.bc * n3 * 2 * sizeof(double)) : 0;
   // two-pass VSS: the partial half spectra of the accumulation's parts 1.. of a launch
   l.off_vp = o;

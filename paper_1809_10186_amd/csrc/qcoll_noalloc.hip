@@ -14,9 +14,28 @@
 
 #include "qcoll_internal.h"
 
+namespace qcoll {
+
+// items per chunk: the plan's chunk, reduced until one chunk's workspace fits the
+// array (the workspace grows with the chunk)
+bool noalloc_layout(const Plan &p, int64_t batch, Layout &lay) {
+  lay = make_layout(p, batch, 0, 1, kScratchBytes);
+  if (lay.total > kScratchBytes) return false;
+  long lo = 1, hi = std::min<long>(batch, p.chunk > 0 ? p.chunk : eval_chunk(p));   // largest chunk that fits
+  while (lo < hi) {
+    const long mid = (lo + hi + 1) / 2;
+    if (make_layout(p, batch, 0, mid, kScratchBytes).total <= kScratchBytes) lo = mid;
+    else hi = mid - 1;
+  }
+  lay = make_layout(p, batch, 0, lo, kScratchBytes);
+  return true;
+}
+
+}  // namespace qcoll
+
 namespace {
 
-constexpr size_t kScratchBytes = size_t(256) << 20;   // 256 MiB per device
+using qcoll::kScratchBytes;
 constexpr int kMaxDevices = 64;
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -60,23 +79,13 @@ extern "C" qcoll_status qcoll_eval_noalloc(qcoll_plan plan, int64_t batch, const
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess) return nfail(QCOLL_EDEVICE, "hipGetDevice failed");
   if (dev != p.device) return nfail(QCOLL_EINVAL, "current device differs from the plan's device");
-  // items per chunk: the plan's chunk, reduced until one chunk's
-  // workspace fits the array (the workspace grows with the chunk)
-  const long want = std::min<long>(batch, p.chunk > 0 ? p.chunk : qcoll::eval_chunk(p));
-  if (qcoll::make_layout(p, batch, 0, 1, 0).total > kScratchBytes)
-    return nfail(QCOLL_EWORKSPACE, "one item of this plan needs " +
-                                       std::to_string(qcoll::make_layout(p, batch, 0, 1, 0).total) +
+  qcoll::Layout lay;
+  if (!qcoll::noalloc_layout(p, batch, lay))
+    return nfail(QCOLL_EWORKSPACE, "one item of this plan needs " + std::to_string(lay.total) +
                                        " bytes of scratch; qcoll_eval_noalloc holds " +
                                        std::to_string(kScratchBytes) + " (use qcoll_eval with a workspace)");
-  long lo = 1, hi = want;   // largest chunk in [1, want] that fits
-  while (lo < hi) {
-    const long mid = (lo + hi + 1) / 2;
-    if (qcoll::make_layout(p, batch, 0, mid, 0).total <= kScratchBytes) lo = mid;
-    else hi = mid - 1;
-  }
   void *ws = nullptr;
   qcoll_status st = scratch_ptr(dev, &ws);
   if (st != QCOLL_OK) return st;
-  const qcoll::Layout lay = qcoll::make_layout(p, batch, 0, lo, kScratchBytes);
   return qcoll::launch_eval(p, batch, f, Q, ws, lay, static_cast<hipStream_t>(stream));
 }

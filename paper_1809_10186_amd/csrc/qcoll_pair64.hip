@@ -24,27 +24,29 @@
 namespace qcoll {
 
 // MODE 0: adjoint, volumes (pair, q); MODE 1: VSS, volumes (pair, q / 2).
-// H: spectra of the items, pairs [bp0, bp0 + nbp) of them; Hp: h_p of every pair
-// (MODE 0); Y: volumes [j1][k2][k3] from pair bp0 on; dots: [2 pairs] parts of
-// <h_p, A_p> by class, or null.
+// H: spectra of the items; the launch takes ni of them from it0 on, nn nodes from n0
+// on of each; Hp: h_p of every pair (MODE 0); Y: the launch's volumes [j1][k2][k3];
+// dots: [2 pairs] parts of <h_p, A_p> by class, or null.
 template <int N, int MODE>
 __global__ __launch_bounds__(C2Geom<N>::NL) void k_terms_c2(const cplx<double> *__restrict__ H,
                                                            const cplx<double> *__restrict__ phase,
                                                            const double *__restrict__ wq,
                                                            const double *__restrict__ Hp,
                                                            cplx<double> *__restrict__ Y, double *__restrict__ dots,
-                                                           long bp0, long nbp, int M, int Nr, double scale) {
+                                                           long it0, long ni, int n0, int nn, int M, int Nr,
+                                                           double scale) {
   using Gm = C2Geom<N>;
   constexpr int NV = Gm::NV, R = Gm::R, S = Gm::S;
   constexpr long n2 = long(N) * N, n3 = n2 * N;
   extern __shared__ double tile[];
 
   const long lb = xcd_block();
-  if (lb >= nbp * 2) return;  // uniform per workgroup
-  const long bpl = lb / 2, bp = bp0 + bpl;
+  if (lb >= ni * nn * 2) return;  // uniform per workgroup
+  const long bpl = lb / 2;
   const int g = int(lb % 2);
-  const long b = bp / Nr;
-  const int p = int(bp % Nr);
+  const long b = it0 + bpl / nn;
+  const int p = n0 + int(bpl % nn);
+  const long bp = b * Nr + p;
   const int lane = threadIdx.x;
   const int vb = lane / N, cb = lane % N;   // plane v and row j2 (k3 after the transpose back)
   const __amdgpu_buffer_rsrc_t hr = make_rsrc(H + b * n3, unsigned(n3 * sizeof(cplx<double>)));
@@ -222,12 +224,13 @@ __device__ __forceinline__ void acc_term(const cplx<double> *__restrict__ y, con
 
 // Z part: one lane per pencil (k2, k3) of an item and per parity of k1, over the
 // volumes of the nodes [part Nr / kAccParts, (part + 1) Nr / kAccParts): a fixed
-// split, so that an item's result does not depend on the launch.
+// split, so that an item's result does not depend on the launch.  A launch of the nodes
+// [n0, n0 + nn) goes on from the sums that the nodes before them left.
 template <int N, int MODE>
 __global__ __launch_bounds__(256, 2) void k_acc_terms(const cplx<double> *__restrict__ Y,
                                                       const cplx<double> *__restrict__ phase,
                                                       const double *__restrict__ apq, cplx<double> *__restrict__ Z,
-                                                      long part_stride, int M, int Nr) {
+                                                      long part_stride, int M, int Nr, int n0, int nn) {
   constexpr int n2 = N * N, HN = N / 2;
   constexpr long n3 = long(n2) * N;
   // a workgroup: 128 pencils, waves 0 and 1 their even k1, waves 2 and 3 the odd
@@ -237,23 +240,32 @@ __global__ __launch_bounds__(256, 2) void k_acc_terms(const cplx<double> *__rest
   const int pen = int(blockIdx.x % GP) * 128 + (wave % 2) * 64 + int(threadIdx.x) % 64;
   const int part = int(blockIdx.y);
   const int p0 = part * Nr / kAccParts, p1 = (part + 1) * Nr / kAccParts;
+  // the part's nodes in this launch; the first launch clears a part without any
+  const int first = p0 > n0 ? p0 : n0, last = p1 < n0 + nn ? p1 : n0 + nn;
+  if (first >= last && !(p0 == p1 && n0 == 0)) return;  // uniform per workgroup
   const int MV = MODE == 0 ? M : (M + 1) / 2;
+  cplx<double> *z = Z + part * part_stride + bl * n3 + pen + (wave / 2) * n2;
   double ar[HN], ai[HN];
   static_for<0, HN>([&](auto i) { ar[decltype(i)::value] = 0.0; ai[decltype(i)::value] = 0.0; });
-  for (int p = p0; p < p1; ++p) {
+  if (first > p0) {
+    static_for<0, HN>([&](auto i) {
+      const cplx<double> v = z[acc_k1<N, 0>(decltype(i)::value) * n2];
+      ar[decltype(i)::value] = v.re;
+      ai[decltype(i)::value] = v.im;
+    });
+  }
+  for (int p = first; p < last; ++p) {
     for (int v = 0; v < MV; ++v) {
       // both parities read a volume together (the second from cache): one barrier
       // that all four waves meet, ahead of the branch on the parity
       __syncthreads();
-      const cplx<double> *y = Y + ((bl * Nr + p) * MV + v) * n3;
+      const cplx<double> *y = Y + ((bl * nn + p - n0) * MV + v) * n3;
       if (wave < 2) acc_term<N, MODE, 0>(y, phase, apq, p, v, M, pen, ar, ai);
       else acc_term<N, MODE, 1>(y, phase, apq, p, v, M, pen, ar, ai);
     }
   }
-  cplx<double> *z = Z + part * part_stride + bl * n3 + pen;
-  const int g = wave / 2;
   static_for<0, HN>([&](auto i) {
-    z[(g + acc_k1<N, 0>(decltype(i)::value)) * n2] = cplx<double>{ar[decltype(i)::value], ai[decltype(i)::value]};
+    z[acc_k1<N, 0>(decltype(i)::value) * n2] = cplx<double>{ar[decltype(i)::value], ai[decltype(i)::value]};
   });
 }
 
@@ -271,8 +283,8 @@ bool use_vss_terms64(const Plan &p) { return terms64_supported(p) && p.schedule 
 
 template <int MODE>
 static qcoll_status launch_terms64(const Plan &p, const cplx<double> *H, const double *Hp, cplx<double> *Y,
-                                   cplx<double> *Z, long part_stride, double *dots, long it0, long ni,
-                                   hipStream_t st) {
+                                   cplx<double> *Z, long part_stride, double *dots, long it0, long ni, int n0,
+                                   int nn, hipStream_t st) {
   constexpr int N = 32;
   using G = C2Geom<N>;
   if (hipFuncSetAttribute(reinterpret_cast<const void *>(&k_terms_c2<N, MODE>),
@@ -281,18 +293,17 @@ static qcoll_status launch_terms64(const Plan &p, const cplx<double> *H, const d
     return QCOLL_EDEVICE;
   }
   const auto *ph = reinterpret_cast<const cplx<double> *>(p.phase);
-  const long nbp = ni * p.N_rho;
   {
     TimedLaunch tl(MODE == 0 ? "vjp terms c2" : "vss terms c2", st);
-    hipLaunchKernelGGL((k_terms_c2<N, MODE>), dim3(unsigned(nbp * 2)), dim3(G::NL), G::lds_bytes, st, H, ph,
-                       reinterpret_cast<const double *>(p.wq), Hp, Y, dots, it0 * p.N_rho, nbp, p.M, p.N_rho,
+    hipLaunchKernelGGL((k_terms_c2<N, MODE>), dim3(unsigned(ni * nn * 2)), dim3(G::NL), G::lds_bytes, st, H, ph,
+                       reinterpret_cast<const double *>(p.wq), Hp, Y, dots, it0, ni, n0, nn, p.M, p.N_rho,
                        1.0 / double(long(N) * N * N));
   }
   {
     TimedLaunch tl(MODE == 0 ? "vjp terms acc" : "vss terms acc", st);
     hipLaunchKernelGGL((k_acc_terms<N, MODE>), dim3(unsigned(ni * (N * N / 128)), kAccParts), dim3(256), 0, st, Y, ph,
                        static_cast<const double *>(p.alpha_pq), Z + it0 * long(N) * N * N, part_stride, p.M,
-                       p.N_rho);
+                       p.N_rho, n0, nn);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) {
@@ -307,7 +318,7 @@ qcoll_status launch_adjoint_terms64(const Plan &p, const void *H, const double *
   for (long i0 = 0; i0 < nb; i0 += pc) {
     const qcoll_status s = launch_terms64<0>(p, static_cast<const cplx<double> *>(H), Hp,
                                              static_cast<cplx<double> *>(Y), static_cast<cplx<double> *>(Z),
-                                             part_stride, dots, i0, nb - i0 < pc ? nb - i0 : pc, st);
+                                             part_stride, dots, i0, nb - i0 < pc ? nb - i0 : pc, 0, p.N_rho, st);
     if (s != QCOLL_OK) return s;
   }
   if (dots) {
@@ -322,12 +333,16 @@ qcoll_status launch_adjoint_terms64(const Plan &p, const void *H, const double *
 }
 
 qcoll_status launch_vss_terms64(const Plan &p, const void *H, void *Y, void *Z, long part_stride, long nb, long pc,
-                                hipStream_t st) {
+                                int pn, hipStream_t st) {
   for (long i0 = 0; i0 < nb; i0 += pc) {
-    const qcoll_status s = launch_terms64<1>(p, static_cast<const cplx<double> *>(H), nullptr,
-                                             static_cast<cplx<double> *>(Y), static_cast<cplx<double> *>(Z),
-                                             part_stride, nullptr, i0, nb - i0 < pc ? nb - i0 : pc, st);
-    if (s != QCOLL_OK) return s;
+    const long ni = nb - i0 < pc ? nb - i0 : pc;
+    for (int n0 = 0; n0 < p.N_rho; n0 += pn) {
+      const qcoll_status s = launch_terms64<1>(p, static_cast<const cplx<double> *>(H), nullptr,
+                                               static_cast<cplx<double> *>(Y), static_cast<cplx<double> *>(Z),
+                                               part_stride, nullptr, i0, ni, n0,
+                                               p.N_rho - n0 < pn ? p.N_rho - n0 : pn, st);
+      if (s != QCOLL_OK) return s;
+    }
   }
   return QCOLL_OK;
 }
