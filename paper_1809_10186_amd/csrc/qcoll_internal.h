@@ -76,6 +76,7 @@ struct Layout {
   size_t off_vp = 0;                                    // two-pass VSS eval: partial half spectra
   size_t off_hg = 0, off_h64g = 0, off_yg = 0;          // bilinear extras
   size_t off_zp = 0;    // FP64 term loops on chip: the kAccParts parts of the items' spectra
+  size_t off_pt = 0;    // FP64 adjoint on chip: the lanes' parts of the omega gradient
   size_t off_u = 0;     // eval of a few items: per-term volumes of the on-chip gain kernels (u_pairs > 0)
   long u_pairs = 0;     // pairs whose M - 1 volumes fit there
   size_t total = 0;
@@ -128,12 +129,14 @@ qcoll_status launch_gain_q64(const Plan &p, const void *H, double *A, void *U, l
 // FP64 term loops on chip with the spectrum of every term's product (N = 32):
 // Z [kAccParts] parts of the items' spectra, part_stride elements apart, their
 // sum in order is the result; Y: pc items' volumes (M a pair, VSS (M + 1) / 2 of pn
-// nodes); dots: two values per pair
+// nodes); dots: two values per pair; parts: term_dot_parts values a pair of pc items
 constexpr int kAccParts = 4;
+inline size_t term_dot_parts(const Plan &p) { return size_t(p.M) * p.N * p.N; }   // two classes of N^2/2 lanes
 bool use_adjoint_terms64(const Plan &p);   // unless the two-pass schedule was requested
 bool use_vss_terms64(const Plan &p);       // unless the schedule is two-pass
 qcoll_status launch_adjoint_terms64(const Plan &p, const void *H, const double *Hp, void *Y, void *Z,
-                                    long part_stride, double *dots, double *dwg, long nb, long pc, hipStream_t st);
+                                    long part_stride, double *dots, double *parts, double *dwg, long nb, long pc,
+                                    hipStream_t st);
 qcoll_status launch_vss_terms64(const Plan &p, const void *H, void *Y, void *Z, long part_stride, long nb, long pc,
                                 int pn, hipStream_t st);
 // schedule 2 exists for this grid and precision (FP32 fused kernel or FP64 on-chip gain)

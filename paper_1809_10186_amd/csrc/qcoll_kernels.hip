@@ -1282,6 +1282,7 @@ Layout make_layout(const Plan &p, int64_t batch, int op, long chunk, size_t ws_b
     l.off_pd = o; o += use_fused_adjoint(p) ? 0 : al(size_t(l.bc) * p.N_rho * p.N * p.N * sizeof(double));
     l.off_yh = o; o += al(size_t(l.pc) * per_item_yh);
     l.off_zp = o; o += t64 ? al(size_t(kAccParts) * l.bc * n3 * 2 * sizeof(double)) : 0;
+    l.off_pt = o; o += t64 ? al(size_t(l.pc) * p.N_rho * term_dot_parts(p) * sizeof(double)) : 0;
     l.total = o;
     // a workspace sized for fewer items than the default chunk
     if (chunk == 0 && l.total > ws_bytes && l.bc > least_chunk(p, op))

@@ -715,7 +715,8 @@ struct Vjp {
       } else if (terms64) {
         if constexpr (std::is_same<T, double>::value && N == 32) {
           const long stride = lay.bc * n3;
-          if ((s = launch_adjoint_terms64(p, H64, Hp, Y, Zp, stride, domega ? pdots : nullptr, dwg, nb, lay.pc, st)))
+          if ((s = launch_adjoint_terms64(p, H64, Hp, Y, Zp, stride, domega ? pdots : nullptr,
+                                          reinterpret_cast<double *>(w + lay.off_pt), dwg, nb, lay.pc, st)))
             return s;
           if ((s = P::template slab<SrcParts<T, N>, DstCplx<T, N>, +1>(SrcParts<T, N>{Zp, stride}, DstCplx<T, N>{Z},
                                                                         nb * N, st, "vjp inverse slab")))
