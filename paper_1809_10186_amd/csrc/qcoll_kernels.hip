@@ -1201,9 +1201,13 @@ bool split_terms(const Plan &p, long nbp) {
   return std::ceil(wgs * n / slots) * t + n * u + 8.0 < t * p.M;
 }
 
-// items per launch of the FP64 on-chip term loops: at N_rho = 16 two workgroups
-// of every pair of 16 items fill 256 CUs twice; more only adds volumes
-constexpr long kTermItems = 16;
+// items per launch of the FP64 on-chip term loops: two workgroups of every one of
+// 256 pairs fill 256 CUs twice, and 16 items the sums; more only adds volumes (VSS,
+// N_rho 4, M 6, 64 items: 537 us at 16 a launch, 446 at 64; 37 items 324, 293)
+static long term_items(const Plan &p) {
+  const long n = (256 + p.N_rho - 1) / p.N_rho;
+  return n < 16 ? 16 : n;
+}
 
 // Items per chunk unless the caller sets it.  Small grids need many items to
 // fill the chip, and a launch costs the same few microseconds for any number:
@@ -1251,7 +1255,7 @@ Layout make_layout(const Plan &p, int64_t batch, int op, long chunk, size_t ws_b
     long pc = long((size_t(4) << 30) / (per_item_y + per_item_yh));
     l.pc = pc < 1 ? 1 : (pc > l.bc ? l.bc : pc);
     if (t64) {
-      if (l.pc > kTermItems) l.pc = kTermItems;
+      if (l.pc > term_items(p)) l.pc = term_items(p);
     } else if (!use_fused_adjoint(p)) {
       // sub-chunks that fill the accumulation kernel's resident workgroups in
       // whole rounds, and chunks of whole sub-chunks (no small tail launch per
@@ -1323,7 +1327,7 @@ Layout make_layout(const Plan &p, int64_t batch, int op, long chunk, size_t ws_b
     const long nodes = long(room / per_node_y);
     l.pn = int(nodes < 1 ? 1 : (nodes > p.N_rho ? p.N_rho : nodes));
     const long pc = nodes / p.N_rho;
-    l.pc = pc < 1 ? 1 : (pc > kTermItems ? kTermItems : pc);
+    l.pc = pc < 1 ? 1 : (pc > term_items(p) ? term_items(p) : pc);
     if (l.pc > l.bc) l.pc = l.bc;
   }
   l.off_h = o; o += al(size_t(l.bc) * n3 * 2 * es);
