@@ -94,12 +94,18 @@ __device__ __forceinline__ void cls_stage_a(__amdgpu_buffer_rsrc_t hr, const cpl
   });
 }
 
-template <int N, int NC>
+// TERM (launches of a few pairs, which leave most CUs idle while each workgroup runs
+// its M terms one after the other): a workgroup per (pair, class, q) stores its u as
+// [j3][j1][j2] in U (term 0: its product, in A); k_gain_acc64 then adds the terms to A_p
+// with the same operations in the same order (one item, N_rho 8, M 12: eval 107 -> 65
+// us, 72 in two passes before their other kernels were merged).
+template <int N, int NC, bool TERM>
 __global__ __launch_bounds__((ClsGeom<N, NC>::NL), 2) void k_gain_cls(const cplx<double> *__restrict__ H,
                                                                       const cplx<double> *__restrict__ phase,
                                                                       const double *__restrict__ wq,
-                                                                      double *__restrict__ A, long nbp, int M, int Nr,
-                                                                      double scale) {
+                                                                      double *__restrict__ A,
+                                                                      cplx<double> *__restrict__ U, long nbp, int M,
+                                                                      int Nr, double scale) {
   using Gm = ClsGeom<N, NC>;
   static_assert(64 % N != 0, "planes straddle waves: workgroup barriers throughout");
   constexpr int NV = Gm::NV, S1 = Gm::S1;
@@ -108,8 +114,8 @@ __global__ __launch_bounds__((ClsGeom<N, NC>::NL), 2) void k_gain_cls(const cplx
   double *tr = cls_lds, *ti = tr + NV * S1;
 
   const long lb = xcd_block();
-  if (lb >= nbp * NC) return;  // uniform per workgroup
-  const long bp = lb / NC;
+  if (lb >= nbp * NC * (TERM ? M : 1)) return;  // uniform per workgroup
+  const long bp = TERM ? lb / NC / M : lb / NC;
   const int g = int(lb % NC);
   const long b = bp / Nr;
   const int p = int(bp % Nr);
@@ -119,11 +125,13 @@ __global__ __launch_bounds__((ClsGeom<N, NC>::NL), 2) void k_gain_cls(const cplx
   double acc[N];
   static_for<0, N>([&](auto j) { acc[decltype(j)::value] = 0.0; });
   const __amdgpu_buffer_rsrc_t hr = make_rsrc(H + b * n3, unsigned(n3 * sizeof(cplx<double>)));
+  const int j1 = g + NC * (vb / 4) + (N / 4) * (vb % 4);
+  const int q0 = TERM ? int(lb / NC % M) : 0, q1 = TERM ? q0 + 1 : M;
   // the axis-1 shift factors of this term and the next
   cplx<double> *b1s = reinterpret_cast<cplx<double> *>(cls_lds + 2 * NV * S1);
-  if (lane < N) b1s[lane] = phase[size_t(p * M) * 3 * N + lane];
+  if (lane < N) b1s[(q0 & 1) * N + lane] = phase[size_t(p * M + q0) * 3 * N + lane];
   __syncthreads();
-  for (int q = 0; q < M; ++q) {
+  for (int q = q0; q < q1; ++q) {
     const cplx<double> *ph = phase + size_t(p * M + q) * 3 * N;
     const double sc = scale * __builtin_sqrt(wq[q]);
     const cplx<double> *b1q = b1s + (q & 1) * N;
@@ -132,7 +140,7 @@ __global__ __launch_bounds__((ClsGeom<N, NC>::NL), 2) void k_gain_cls(const cplx
       if (g == decltype(gg)::value) cls_stage_a<N, NC, decltype(gg)::value>(hr, ph, b1q, lane, sc, tr, ti);
     });
     // the next term's factors: their slot was last read before stage A's barrier
-    if (lane < N && q + 1 < M) b1s[((q + 1) & 1) * N + lane] = ph[3 * N + lane];
+    if (lane < N && q + 1 < q1) b1s[((q + 1) & 1) * N + lane] = ph[3 * N + lane];
     __syncthreads();
     static_for<0, N>([&](auto kk) {
       zr[decltype(kk)::value] = tr[vb * S1 + decltype(kk)::value * N + cb];
@@ -151,13 +159,22 @@ __global__ __launch_bounds__((ClsGeom<N, NC>::NL), 2) void k_gain_cls(const cplx
       zi[decltype(kk)::value] = ti[vb * S1 + decltype(kk)::value * (N + 1) + cb];
     });
     fft_reg<N, +1, double>(zr, zi);   // axis 3: lane (v, j2) holds j3 = 0..N-1
+    if constexpr (TERM) {
+      if (q > 0) {
+        cplx<double> *u = U + (bp * (M - 1) + q - 1) * n3 + j1 * N + cb;
+        static_for<0, N>([&](auto j) {
+          constexpr int jj = decltype(j)::value;
+          u[jj * n2] = cplx<double>{zr[jj], zi[jj]};
+        });
+        return;
+      }
+    }
     static_for<0, N>([&](auto j) {
       constexpr int jj = decltype(j)::value;
-      acc[jj] += zr[jj] * zr[jj];
-      acc[jj] -= zi[jj] * zi[jj];
+      acc[jj] = __builtin_fma(zr[jj], zr[jj], acc[jj]);
+      acc[jj] = __builtin_fma(-zi[jj], zi[jj], acc[jj]);
     });
   }
-  const int j1 = g + NC * (vb / 4) + (N / 4) * (vb % 4);
   double2 *a = reinterpret_cast<double2 *>(A + bp * n3 + j1 * n2 + long(cb) * N);
   static_for<0, N / 2>([&](auto j) {
     constexpr int jj = decltype(j)::value;
@@ -165,24 +182,12 @@ __global__ __launch_bounds__((ClsGeom<N, NC>::NL), 2) void k_gain_cls(const cplx
   });
 }
 
-qcoll_status launch_gain_cls24(const Plan &p, const void *H, double *A, long nbp, hipStream_t st) {
+qcoll_status launch_gain_cls24(const Plan &p, const void *H, double *A, void *U, long nbp, hipStream_t st) {
   constexpr int N = 24, NC = 3;
   using G = ClsGeom<N, NC>;
-  if (hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gain_cls<N, NC>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, int(G::lds_bytes)) != hipSuccess) {
-    set_error("hipFuncSetAttribute failed for the class gain kernel");
-    return QCOLL_EDEVICE;
-  }
-  TimedLaunch tl("gain classes", st);
-  hipLaunchKernelGGL((k_gain_cls<N, NC>), dim3(unsigned(nbp * NC)), dim3(G::NL), G::lds_bytes, st,
-                     static_cast<const cplx<double> *>(H), reinterpret_cast<const cplx<double> *>(p.phase),
-                     reinterpret_cast<const double *>(p.wq), A, nbp, p.M, p.N_rho, 1.0 / double(long(N) * N * N));
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) {
-    set_error(std::string("gain classes: ") + hipGetErrorString(e));
-    return QCOLL_EDEVICE;
-  }
-  return QCOLL_OK;
+  return launch_onchip64<N, NC, N>(p, U ? &k_gain_cls<N, NC, true> : &k_gain_cls<N, NC, false>, G::NL, G::lds_bytes,
+                                   "gain classes", static_cast<const cplx<double> *>(H), A,
+                                   static_cast<cplx<double> *>(U), nbp, st);
 }
 
 }  // namespace qcoll

@@ -286,58 +286,6 @@ __global__ __launch_bounds__(C2Geom<N>::NL) void k_gain_c2(const cplx<double> *_
   });
 }
 
-// A_p += Re(u_q)^2 - Im(u_q)^2, q = 1..M-1, from the volumes TERM stored, one
-// point per lane; with N > 0 they are laid out [j3][j1][j2]
-template <int N>
-__global__ __launch_bounds__(256) void k_gain_acc64(const double2 *__restrict__ U, double *__restrict__ A, long n3,
-                                                    long nbp, int nq) {
-  const long i = long(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= nbp * n3) return;
-  const long bp = i / n3, o = i % n3;
-  const double2 *u = U + bp * nq * n3 + o;
-  long d = o;
-  if constexpr (N > 0) d = (o % (N * N)) * N + o / (N * N);
-  double a = A[bp * n3 + d];
-#pragma unroll 6
-  for (int q = 0; q < nq; ++q) {
-    const double2 v = u[q * n3];
-    a = __builtin_fma(v.x, v.x, a);
-    a = __builtin_fma(-v.y, v.y, a);
-  }
-  A[bp * n3 + d] = a;
-}
-
-// the whole term loop per workgroup, or with U (nbp * (M - 1) volumes) a
-// workgroup per term and the sum over the terms after it
-template <int N, int CLASSES, int PERM, class Kern>
-static qcoll_status launch_onchip64(const Plan &p, Kern kern, int lanes, size_t lds, const char *what,
-                                    const cplx<double> *H, double *A, cplx<double> *U, long nbp, hipStream_t st) {
-  if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                          int(lds)) != hipSuccess) {
-    set_error("hipFuncSetAttribute failed for the FP64 gain kernel");
-    return QCOLL_EDEVICE;
-  }
-  constexpr long n3 = long(N) * N * N;
-  {
-    TimedLaunch tl(what, st);
-    const double scale = 1.0 / double(n3);
-    hipLaunchKernelGGL(kern, dim3(unsigned(nbp * CLASSES * (U ? p.M : 1))), dim3(lanes), lds, st, H,
-                       reinterpret_cast<const cplx<double> *>(p.phase), reinterpret_cast<const double *>(p.wq), A, U,
-                       nbp, p.M, p.N_rho, scale);
-  }
-  if (U) {
-    TimedLaunch tl("gain acc", st);
-    hipLaunchKernelGGL((k_gain_acc64<PERM>), dim3(unsigned((nbp * n3 + 255) / 256)), dim3(256), 0, st,
-                       reinterpret_cast<const double2 *>(U), A, n3, nbp, p.M - 1);
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) {
-    set_error(std::string(what) + ": " + hipGetErrorString(e));
-    return QCOLL_EDEVICE;
-  }
-  return QCOLL_OK;
-}
-
 bool gain_q64_supported(int N, int precision) { return precision == QCOLL_FP64 && (N == 16 || N == 32); }
 
 bool use_gain_q64(const Plan &p) {
@@ -355,7 +303,7 @@ qcoll_status launch_gain_q64(const Plan &p, const void *H, double *A, void *U, l
     case 16:
       return launch_onchip64<16, 4, 0>(p, u ? &k_gain_q64<16, true> : &k_gain_q64<16, false>, G16::NL,
                                        G16::lds_bytes, "gain q64", h, A, u, nbp, st);
-    case 24: return launch_gain_cls24(p, h, A, nbp, st);   // never split by terms
+    case 24: return launch_gain_cls24(p, h, A, U, nbp, st);
     case 32:
       return launch_onchip64<32, 2, 32>(p, u ? &k_gain_c2<32, true> : &k_gain_c2<32, false>, G32::NL,
                                         G32::lds_bytes, "gain c2", h, A, u, nbp, st);

@@ -120,9 +120,8 @@ qcoll_status launch_gain_fused(const Plan &p, const void *H, void *W, void *U, l
 // [j1][j2][j3]; S: cap complex volumes of scratch
 qcoll_status launch_gain_bil(const Plan &p, const void *Hf, const void *Hg, void *A, void *S, long cap, long nbp,
                              hipStream_t st);
-// FP64 gain loop on chip (N = 16, 24, 32): A_p of every (item, node) pair; U as
-// above (null at N = 24)
-qcoll_status launch_gain_cls24(const Plan &p, const void *H, double *A, long nbp, hipStream_t st);
+// FP64 gain loop on chip (N = 16, 24, 32): A_p of every (item, node) pair; U as above
+qcoll_status launch_gain_cls24(const Plan &p, const void *H, double *A, void *U, long nbp, hipStream_t st);
 bool gain_q64_supported(int N, int precision);
 bool use_gain_q64(const Plan &p);
 qcoll_status launch_gain_q64(const Plan &p, const void *H, double *A, void *U, long nbp, hipStream_t st);

@@ -1180,7 +1180,9 @@ bool use_fused_gain(const Plan &p) {
 // pair against per term: FP32 12^3 42 -> 28 us, 16^3 52 -> 33, 24^3 93 -> 53
 // (four items 94 -> 78, and level at six),
 // 32^3 156 -> 74 (two items 158 -> 95, three 159 -> 121, and level at four);
-// FP64 16^3 107 -> 54, 32^3 212 -> 121.  At 8^3 the launches cost what it gains.
+// FP64 16^3 107 -> 54, 24^3 110 -> 80 (two items 112 -> 100, and level at three; a CU
+// holds two of its workgroups, at two thirds of the speed), 32^3 212 -> 121.  At 8^3
+// the launches cost what it gains.
 bool split_terms(const Plan &p, long nbp) {
   if (p.is_vss() || p.M < 2 || !(use_fused_gain(p) || use_gain_q64(p))) return false;
   const bool dp = p.precision == QCOLL_FP64;
@@ -1188,10 +1190,7 @@ bool split_terms(const Plan &p, long nbp) {
   switch (p.N) {
     case 12: t = 2.0; slots = 1024; break;
     case 16: t = dp ? 6.5 : 2.5; slots = dp ? 2048 : 1024; wgs = dp ? 4.0 : 1.0; break;
-    case 24:
-      if (dp) return false;
-      t = 5.2; slots = 256;
-      break;
+    case 24: t = dp ? 6.3 : 5.2; slots = dp ? 384 : 256; wgs = dp ? 3.0 : 1.0; break;
     case 32: t = dp ? 12.0 : 9.5; slots = 256; wgs = dp ? 2.0 : 1.0; break;
     default: return false;
   }
