@@ -234,11 +234,11 @@ struct OpLowRank {
   const T *V;
   C<double> *TA;
   int npair;
-  // the sum over the pairs [s0, s1)
-  __device__ __forceinline__ void sum(long b, int r, int s0, int s1, T *tr, T *ti) const {
+  __device__ void operator()(long b, int r) const {
     constexpr long n2 = long(N) * N, n3 = n2 * N;
+    T tr[N], ti[N];
     static_for<0, N>([&](auto k) { tr[decltype(k)::value] = T(0); ti[decltype(k)::value] = T(0); });
-    for (int s = s0; s < s1; ++s) {
+    for (int s = 0; s < npair; ++s) {
       const C<double> *w = W + (b * npair + s) * n3 + r;
       T xr[N], xi[N];
       static_for<0, N>([&](auto k) {
@@ -274,16 +274,11 @@ struct OpLowRank {
           constexpr int kk = k0 + decltype(ii)::value;
           const T a = av[decltype(ii)::value], c = cv[decltype(ii)::value];
           // (a - i c)(xr + i xi) = (a xr + c xi) + i (a xi - c xr)
-          tr[kk] += a * xr[kk] + c * xi[kk];
-          ti[kk] += a * xi[kk] - c * xr[kk];
+          tr[kk] += __builtin_fma(a, xr[kk], c * xi[kk]);
+          ti[kk] += __builtin_fma(a, xi[kk], -(c * xr[kk]));
         });
       });
     }
-  }
-  __device__ void operator()(long b, int r) const {
-    constexpr long n2 = long(N) * N, n3 = n2 * N;
-    T tr[N], ti[N];
-    sum(b, r, 0, npair, tr, ti);
     C<double> *o = TA + b * n3 + r;
     static_for<0, N>([&](auto k) {
       o[decltype(k)::value * n2] = C<double>{double(tr[decltype(k)::value]), double(ti[decltype(k)::value])};
@@ -291,68 +286,86 @@ struct OpLowRank {
   }
 };
 
-// Grids up to 32^3: the pairs in four fixed parts, added in order.  For few items
-// (16 waves for one of 32^3) the pass is a chain of load and transform per pair, so
-// k_low_rank_parts gives each part a wave of a workgroup of 64 pencils; for many it
-// is bound by the reads of W and loses by that workgroup's reduction, so
-// k_low_rank_chain takes the parts in turn, the total in LDS (the registers hold one
-// part's sum and a pencil).  The same bits.  16 nodes (8 pairs) at 32^3, 8 else, one
-// chain without parts before: 1 item at 32^3 36 -> 16 us, 24^3 15 -> 9, 16^3 11 -> 7.4,
-// 1024 at 12^3 36 -> 27; in turn 192 at 32^3 202 -> 218 us, 100 at 24^3 26 -> 27, 512 at
-// 16^3 39 -> 38 (side by side 247, 29 and 44).
-constexpr int kLowRankParts = 4;
+// The same sums for few items up to 32^3 (16 waves for one of 32^3, each a chain of
+// load and transform per pair): of a workgroup's 64 pencils each of its four waves
+// transforms one pair at a time into LDS, and then adds all four, in order, to a
+// quarter of the outputs.  The operations on a value and their order are OpLowRank's
+// (its products are explicit fused operations for that): the same bits.
+constexpr int kLowRankWaves = 4;
+// from 24^3 on the outputs go through LDS in two halves (48 KiB, 64 KiB at 32^3), so
+// that workgroups share a CU
+constexpr int low_rank_halves(int N) { return N >= 24 ? 2 : 1; }
 
 template <int N>
-__global__ __launch_bounds__(64 * kLowRankParts) void k_low_rank_parts(OpLowRank<double, N> op, long npencil) {
+__global__ __launch_bounds__(64 * kLowRankWaves, N >= 24 ? 2 : 4) void k_low_rank_few(OpLowRank<double, N> op,
+                                                                                     long npencil) {
   constexpr long n2 = long(N) * N, n3 = n2 * N;
-  __shared__ double sums[kLowRankParts - 1][N][64];
-  const int lane = int(threadIdx.x) % 64, part = int(threadIdx.x) / 64;
+  constexpr int H = low_rank_halves(N), NH = N / H, NO = NH / kLowRankWaves;   // outputs of a half, a wave's of them
+  static_assert(N % (H * kLowRankWaves) == 0, "whole outputs a wave");
+  __shared__ double pairs[kLowRankWaves][2][NH][64];
+  const int lane = int(threadIdx.x) % 64, wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) / 64);
   const long pen = long(blockIdx.x) * 64 + lane;
   const long pl = pen < npencil ? pen : npencil - 1;   // lanes past the end load it and store nothing
   const long b = pl / n2;
   const int r = int(pl % n2);
-  double tr[N], ti[N];
-  op.sum(b, r, (part * op.npair) / kLowRankParts, ((part + 1) * op.npair) / kLowRankParts, tr, ti);
-  auto add = [&](double *t) {
-    if (part > 0) static_for<0, N>([&](auto k) { sums[part - 1][decltype(k)::value][lane] = t[decltype(k)::value]; });
-    __syncthreads();
-    if (part == 0) {
-#pragma unroll
-      for (int i = 0; i < kLowRankParts - 1; ++i)
-        static_for<0, N>([&](auto k) { t[decltype(k)::value] += sums[i][decltype(k)::value][lane]; });
+  double tr[H][NO], ti[H][NO];
+  static_for<0, H * NO>([&](auto i) {
+    tr[decltype(i)::value / NO][decltype(i)::value % NO] = 0.0;
+    ti[decltype(i)::value / NO][decltype(i)::value % NO] = 0.0;
+  });
+  for (int s0 = 0; s0 < op.npair; s0 += kLowRankWaves) {
+    double xr[N], xi[N];
+    if (s0 + wave < op.npair) {
+      const C<double> *w = op.W + (b * op.npair + s0 + wave) * n3 + r;
+      static_for<0, N>([&](auto k) {
+        const C<double> e = w[decltype(k)::value * n2];
+        xr[decltype(k)::value] = e.re;
+        xi[decltype(k)::value] = e.im;
+      });
+      fft_reg<N, -1, double>(xr, xi);
     }
-  };
-  add(tr);
-  __syncthreads();
-  add(ti);
-  if (part == 0 && pen < npencil) {
-    C<double> *o = op.TA + b * n3 + r;
-    static_for<0, N>([&](auto k) { o[decltype(k)::value * n2] = C<double>{tr[decltype(k)::value], ti[decltype(k)::value]}; });
+    static_for<0, H>([&](auto hh) {
+      constexpr int h = decltype(hh)::value;
+      // the factors of all four pairs are on their way while the values are exchanged
+      // (a pair past the last one: the last one's, unused)
+      double av[kLowRankWaves][NO], cv[kLowRankWaves][NO];
+      static_for<0, kLowRankWaves>([&](auto j) {
+        const int s = s0 + decltype(j)::value < op.npair ? s0 + decltype(j)::value : op.npair - 1;
+        const double *v0 = op.V + (2 * s) * n3 + (h * NH + wave * NO) * n2 + r, *v1 = v0 + n3;
+        static_for<0, NO>([&](auto i) {
+          av[decltype(j)::value][decltype(i)::value] = v0[decltype(i)::value * n2];
+          cv[decltype(j)::value][decltype(i)::value] = v1[decltype(i)::value * n2];
+        });
+      });
+      __builtin_amdgcn_sched_barrier(0);
+      if (s0 + wave < op.npair) {
+        static_for<0, NH>([&](auto k) {
+          pairs[wave][0][decltype(k)::value][lane] = xr[h * NH + decltype(k)::value];
+          pairs[wave][1][decltype(k)::value][lane] = xi[h * NH + decltype(k)::value];
+        });
+      }
+      __syncthreads();
+      static_for<0, kLowRankWaves>([&](auto j) {
+        constexpr int jj = decltype(j)::value;
+        if (s0 + jj < op.npair) {   // uniform
+          static_for<0, NO>([&](auto i) {
+            constexpr int ii = decltype(i)::value;
+            const double a = av[jj][ii], c = cv[jj][ii];
+            const double x = pairs[jj][0][wave * NO + ii][lane], y = pairs[jj][1][wave * NO + ii][lane];
+            tr[h][ii] += __builtin_fma(a, x, c * y);
+            ti[h][ii] += __builtin_fma(a, y, -(c * x));
+          });
+        }
+      });
+      __syncthreads();
+    });
   }
-}
-
-template <int N>
-__global__ __launch_bounds__(64) void k_low_rank_chain(OpLowRank<double, N> op, long npencil) {
-  constexpr long n2 = long(N) * N, n3 = n2 * N;
-  __shared__ double total[2][N][64];   // a column per lane
-  const int lane = int(threadIdx.x);
-  const long pen = long(blockIdx.x) * 64 + lane;
-  if (pen >= npencil) return;
-  const long b = pen / n2;
-  const int r = int(pen % n2);
-  C<double> *o = op.TA + b * n3 + r;
-  for (int part = 0; part < kLowRankParts; ++part) {
-    double tr[N], ti[N];
-    op.sum(b, r, (part * op.npair) / kLowRankParts, ((part + 1) * op.npair) / kLowRankParts, tr, ti);
-    if (part > 0) static_for<0, N>([&](auto k) {
-      tr[decltype(k)::value] = total[0][decltype(k)::value][lane] + tr[decltype(k)::value];
-      ti[decltype(k)::value] = total[1][decltype(k)::value][lane] + ti[decltype(k)::value];
+  if (pen < npencil) {
+    C<double> *o = op.TA + b * n3 + wave * NO * n2 + r;
+    static_for<0, H * NO>([&](auto i) {
+      constexpr int h = decltype(i)::value / NO, ii = decltype(i)::value % NO;
+      o[(h * NH + ii) * n2] = C<double>{tr[h][ii], ti[h][ii]};
     });
-    if (part < kLowRankParts - 1) static_for<0, N>([&](auto k) {
-      total[0][decltype(k)::value][lane] = tr[decltype(k)::value];
-      total[1][decltype(k)::value][lane] = ti[decltype(k)::value];
-    });
-    else static_for<0, N>([&](auto k) { o[decltype(k)::value * n2] = C<double>{tr[decltype(k)::value], ti[decltype(k)::value]}; });
   }
 }
 
@@ -848,6 +861,15 @@ struct OpLowRankC {
   }
 };
 
+// Launches of wgs workgroups of 64 pencils that k_low_rank_few takes: two a CU at
+// 32^3, four at 16^3, nine at 24^3 (256 items), below 16^3 all.  8 pairs, in turn / side
+// by side: 32^3 1 item 36 -> 15 us, 32 items 53 -> 37, 64 items 66 / 83; 24^3 1 item
+// 25 -> 13, 64 items 39 -> 33, 256 items 145 -> 135 (6 pairs level at 112); 16^3 1 item
+// 17 -> 10, 256 items 35 -> 33, 1024 items 141 / 153; 12^3 1024 items 65 -> 60; 8^3 24 -> 20.
+static bool low_rank_few(int N, unsigned wgs) {
+  return N < 16 || wgs <= (N == 16 ? 1024u : (N == 24 ? 2304u : 512u));
+}
+
 // How many of nbp pairs, from the front, go through the bilinear gain loop on
 // chip; the rest takes the two passes, with the same bits.  The passes' time
 // grows with the pairs; the chip's with every full set of workgroups, 256 pairs
@@ -1142,16 +1164,14 @@ struct Engine {
         return s;
       OpLowRank<double, N> lr{Wd, p.v64(), TA, np};
       if constexpr (N <= 32) {
-        TimedLaunch tl("low-rank pencil", st);
-        // parts side by side while their workgroups are at most one (32^3: 16 items
-        // 22 us against 36 in turn, 64 95 against 74) or two a CU (24^3: 30 items 14 /
-        // 17, 100 29 / 27; 16^3: 128 items level at 13); below 16^3 always
         const unsigned wgs = nblk(nb * N * N, 64);
-        if (N < 16 || wgs <= (N == 32 ? 256u : 512u))
-          hipLaunchKernelGGL((k_low_rank_parts<N>), dim3(wgs), dim3(64 * kLowRankParts), 0, st, lr, nb * N * N);
-        else
-          hipLaunchKernelGGL((k_low_rank_chain<N>), dim3(wgs), dim3(64), 0, st, lr, nb * N * N);
-        QC_LAUNCH_CHECK("low-rank pencil");
+        if (low_rank_few(N, wgs)) {
+          TimedLaunch tl("low-rank pencil", st);
+          hipLaunchKernelGGL((k_low_rank_few<N>), dim3(wgs), dim3(64 * kLowRankWaves), 0, st, lr, nb * N * N);
+          QC_LAUNCH_CHECK("low-rank pencil");
+        } else if ((s = pencil(lr, nb * N * N, st, "low-rank pencil"))) {
+          return s;
+        }
       } else {
         if ((s = pencil(lr, nb * N * N, st, "low-rank pencil"))) return s;
       }
