@@ -325,22 +325,47 @@ size_t qcoll_autotune_workspace_bytes(qcoll_plan plan, int64_t batch) {
   return autotune_bytes(plan, batch, ~size_t(0));
 }
 
-// Cache entries carry the schedule set they were timed against ("s2": the FP32
-// fused kernels, the FP64 on-chip kernels at 16^3 and 32^3); a build that adds
-// or changes a schedule bumps it, so that an older entry is timed again
-// instead of pinning a plan to what used to be the faster schedule ("s3": the
-// FP64 on-chip loops at 24^3 and, for VSS kernels, at 32^3).
-static int tune_schedule_set(const qcoll::Plan &p) {
-  return p.precision == QCOLL_FP64 && (p.N == 24 || (p.N == 32 && p.is_vss())) ? 3 : 2;
+// Cache entries carry the schedule set they were timed against; a build that
+// adds or changes a schedule or its candidate chunks bumps it, so that an older
+// entry is timed again instead of pinning a plan to what used to be the faster
+// choice.  Set 2 stays where neither changed: above 32^3, and at 8^3 up to the 256
+// items that its candidates always held.
+static int tune_schedule_set(const qcoll::Plan &p, int64_t batch) {
+  return p.N > 32 || (p.N == 8 && batch <= 256) ? 2 : 4;
 }
 
+// VSS and literal plans have other candidates than the VHS plan of the same sizes
 static std::string tune_key(const qcoll::Plan &p, int64_t batch) {
   int bucket = 1;
   while (bucket < batch && bucket < (1 << 20)) bucket <<= 1;
   std::ostringstream k;
-  k << "gfx950 s" << tune_schedule_set(p) << " N=" << p.N << " Nr=" << p.N_rho << " M=" << p.M
-    << " prec=" << p.precision << " rank=" << p.rank << " batch<=" << bucket;
+  k << "gfx950 s" << tune_schedule_set(p, batch) << " N=" << p.N << " Nr=" << p.N_rho << " M=" << p.M
+    << " prec=" << p.precision << " rank=" << p.rank << (p.is_vss() ? " vss" : "") << (p.literal ? " literal" : "")
+    << " batch<=" << bucket;
   return k.str();
+}
+
+extern "C++" bool qcoll::tune_cache_find(const Plan &p, int64_t batch, const char *file, int &schedule, int &chunk) {
+  const std::string key = tune_key(p, batch);
+  std::ifstream in(file);
+  std::string line;
+  while (std::getline(in, line)) {
+    const size_t bar = line.find('|');
+    if (bar == std::string::npos || line.substr(0, bar) != key) continue;
+    // "<schedule> <chunk> [ms]": a candidate schedule, chunk 1..65536; anything
+    // else (garbage, out-of-range numbers) is skipped
+    const char *c0 = line.c_str() + bar + 1;
+    char *e1 = nullptr, *e2 = nullptr;
+    errno = 0;
+    const long sch = std::strtol(c0, &e1, 10);
+    const long ck = (e1 != c0) ? std::strtol(e1, &e2, 10) : 0;
+    if (errno == 0 && e1 != c0 && e2 && e2 != e1 && (sch == 1 || sch == onchip_candidate(p)) && ck >= 1 && ck <= 65536) {
+      schedule = int(sch);
+      chunk = int(ck);
+      return true;
+    }
+  }
+  return false;
 }
 
 qcoll_status qcoll_autotune(qcoll_plan plan, int64_t batch, const double *f, double *Q, void *ws, size_t ws_bytes,
@@ -351,32 +376,15 @@ qcoll_status qcoll_autotune(qcoll_plan plan, int64_t batch, const double *f, dou
   qcoll::Plan &p = plan->p;
   const std::string key = tune_key(p, batch);
   const char *cache = std::getenv("QCOLL_AUTOTUNE_CACHE");
-  if (cache) {
-    std::ifstream in(cache);
-    std::string line;
-    while (std::getline(in, line)) {
-      const size_t bar = line.find('|');
-      if (bar == std::string::npos || line.substr(0, bar) != key) continue;
-      // "<schedule> <chunk> [ms]": a candidate schedule, chunk 1..65536; anything
-      // else (garbage, out-of-range numbers) is skipped
-      const char *c0 = line.c_str() + bar + 1;
-      char *e1 = nullptr, *e2 = nullptr;
-      errno = 0;
-      const long sch_l = std::strtol(c0, &e1, 10);
-      const long ck_l = (e1 != c0) ? std::strtol(e1, &e2, 10) : 0;
-      const bool parsed = errno == 0 && e1 != c0 && e2 && e2 != e1 && (sch_l == 1 || sch_l == onchip_candidate(p)) && ck_l >= 1 &&
-                          ck_l <= 65536;
-      const int sch = int(sch_l), ck = int(ck_l);
-      if (parsed) {
-        p.schedule = sch;
-        p.chunk = ck;
-        ++p.gen;
-        qcoll::log("autotune %s: cached schedule %d chunk %d (%s)", key.c_str(), sch, ck, cache);
-        if (host_schedule) *host_schedule = sch;
-        if (host_chunk) *host_chunk = ck;
-        return QCOLL_OK;
-      }
-    }
+  int sch = 0, ck = 0;
+  if (cache && qcoll::tune_cache_find(p, batch, cache, sch, ck)) {
+    p.schedule = sch;
+    p.chunk = ck;
+    ++p.gen;
+    qcoll::log("autotune %s: cached schedule %d chunk %d (%s)", key.c_str(), sch, ck, cache);
+    if (host_schedule) *host_schedule = sch;
+    if (host_chunk) *host_chunk = ck;
+    return QCOLL_OK;
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
   hipEvent_t e0, e1;

@@ -1,4 +1,4 @@
-// Workspace layouts of the library on the host alone (no device): prints one
+// Workspace layouts and the autotune cache of the library on the host alone (no device): prints one
 // "FAILED ..." line per broken expectation and "layouts: ok" at the end.
 #include <cstdio>
 #include <cstring>
@@ -53,9 +53,40 @@ static void check_noalloc() {
           }
 }
 
+static void write_cache(const char *file, const char *text) {
+  FILE *fp = std::fopen(file, "w");
+  if (fp) {
+    std::fputs(text, fp);
+    std::fclose(fp);
+  }
+}
+
+// entries of another kernel kind, Nyquist convention or schedule set are not this plan's
+static void check_tune_key(const char *file) {
+  const qcoll::Plan vhs = plan_of(24, 8, 12, QCOLL_FP64), vss = plan_of(24, 8, 12, QCOLL_FP64, 1.5),
+                    lit = plan_of(24, 8, 12, QCOLL_FP64, 1.0, true);
+  int sch = -7, ck = -7;
+  write_cache(file, "gfx950 s2 N=24 Nr=8 M=12 prec=0 rank=8 batch<=64|1 32\n"
+                    "gfx950 s3 N=24 Nr=8 M=12 prec=0 rank=8 batch<=64|1 32\n");
+  EXPECT(!qcoll::tune_cache_find(vhs, 50, file, sch, ck), "older set");
+  write_cache(file, "gfx950 s4 N=24 Nr=8 M=12 prec=0 rank=8 vss batch<=64|1 32\n"
+                    "gfx950 s4 N=24 Nr=8 M=12 prec=0 rank=8 literal batch<=64|1 96\n");
+  EXPECT(!qcoll::tune_cache_find(vhs, 50, file, sch, ck), "VHS plan, VSS and literal entries");
+  EXPECT(qcoll::tune_cache_find(vss, 50, file, sch, ck) && sch == 1 && ck == 32, "%d %d", sch, ck);
+  EXPECT(qcoll::tune_cache_find(lit, 50, file, sch, ck) && sch == 1 && ck == 96, "%d %d", sch, ck);
+  EXPECT(!qcoll::tune_cache_find(vss, 65, file, sch, ck), "another batch");
+  // small grids: larger candidates above 256 items, the older entries below
+  const qcoll::Plan small = plan_of(8, 4, 6, QCOLL_FP32);
+  write_cache(file, "gfx950 s2 N=8 Nr=4 M=6 prec=1 rank=4 batch<=256|2 192\n"
+                    "gfx950 s2 N=8 Nr=4 M=6 prec=1 rank=4 batch<=512|2 256\n");
+  EXPECT(qcoll::tune_cache_find(small, 256, file, sch, ck) && sch == 2 && ck == 192, "%d %d", sch, ck);
+  EXPECT(!qcoll::tune_cache_find(small, 300, file, sch, ck), "256 items were the largest candidate");
+}
+
 int main(int argc, char **argv) {
   const char *what = argc > 1 ? argv[1] : "";
   if (!std::strcmp(what, "noalloc")) check_noalloc();
+  else if (!std::strcmp(what, "tune_key") && argc > 2) check_tune_key(argv[2]);
   else return 2;
   if (g_fail) {
     std::printf("layouts: %d failures\n", g_fail);

@@ -1,4 +1,4 @@
-"""Workspace layouts on the host (tests/host_check/layouts.cpp, compiled here against the built library): no device."""
+"""Workspace layouts and the autotuner's cache on the host (tests/host_check/layouts.cpp, compiled here against the built library): no device."""
 import os
 import subprocess
 
@@ -22,8 +22,8 @@ def driver(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("what", ["noalloc"])
-def test_layouts(driver, what):
-    r = subprocess.run([driver, what], capture_output=True, text=True, timeout=300)
+@pytest.mark.parametrize("what", ["noalloc", "tune_key"])
+def test_layouts(driver, tmp_path, what):
+    r = subprocess.run([driver, what, str(tmp_path / "cache.txt")], capture_output=True, text=True, timeout=300)
     print(r.stdout[-3000:], r.stderr[-1000:], flush=True)
     assert r.returncode == 0 and "layouts: ok" in r.stdout
