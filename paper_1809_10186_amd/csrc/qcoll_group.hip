@@ -359,7 +359,8 @@ extern "C++" bool qcoll::tune_cache_find(const Plan &p, int64_t batch, const cha
     errno = 0;
     const long sch = std::strtol(c0, &e1, 10);
     const long ck = (e1 != c0) ? std::strtol(e1, &e2, 10) : 0;
-    if (errno == 0 && e1 != c0 && e2 && e2 != e1 && (sch == 1 || sch == onchip_candidate(p)) && ck >= 1 && ck <= 65536) {
+    const bool candidate = sch == 1 || (sch >= 0 && sch == onchip_candidate(p));   // -1: no on-chip one
+    if (errno == 0 && e1 != c0 && e2 && e2 != e1 && candidate && ck >= 1 && ck <= 65536) {
       schedule = int(sch);
       chunk = int(ck);
       return true;

@@ -83,10 +83,25 @@ static void check_tune_key(const char *file) {
   EXPECT(!qcoll::tune_cache_find(small, 300, file, sch, ck), "256 items were the largest candidate");
 }
 
+// schedules that are no candidate of the plan, negative ones among them
+static void check_tune_schedule(const char *file) {
+  write_cache(file, "gfx950 s4 N=24 Nr=8 M=12 prec=0 rank=8 vss batch<=64|-1 64\n"
+                    "gfx950 s4 N=24 Nr=8 M=12 prec=0 rank=8 vss batch<=64|0 64\n"
+                    "gfx950 s4 N=24 Nr=8 M=12 prec=0 rank=8 vss batch<=64|2 64\n"
+                    "gfx950 s4 N=24 Nr=8 M=12 prec=0 rank=8 batch<=64|-1 64\n"
+                    "gfx950 s4 N=24 Nr=8 M=12 prec=0 rank=8 batch<=64|2 64\n"
+                    "gfx950 s4 N=24 Nr=8 M=12 prec=0 rank=8 batch<=64|0 40\n");
+  int sch = -7, ck = -7;
+  EXPECT(!qcoll::tune_cache_find(plan_of(24, 8, 12, QCOLL_FP64, 1.5), 50, file, sch, ck), "%d %d", sch, ck);
+  EXPECT(qcoll::tune_cache_find(plan_of(24, 8, 12, QCOLL_FP64), 50, file, sch, ck) && sch == 0 && ck == 40, "%d %d", sch,
+         ck);
+}
+
 int main(int argc, char **argv) {
   const char *what = argc > 1 ? argv[1] : "";
   if (!std::strcmp(what, "noalloc")) check_noalloc();
   else if (!std::strcmp(what, "tune_key") && argc > 2) check_tune_key(argv[2]);
+  else if (!std::strcmp(what, "tune_schedule") && argc > 2) check_tune_schedule(argv[2]);
   else return 2;
   if (g_fail) {
     std::printf("layouts: %d failures\n", g_fail);
