@@ -345,7 +345,8 @@ static std::string tune_key(const qcoll::Plan &p, int64_t batch) {
   return k.str();
 }
 
-extern "C++" bool qcoll::tune_cache_find(const Plan &p, int64_t batch, const char *file, int &schedule, int &chunk) {
+extern "C++" bool qcoll::tune_cache_find(const Plan &p, int64_t batch, size_t ws_bytes, const char *file,
+                                        int &schedule, int &chunk) {
   const std::string key = tune_key(p, batch);
   std::ifstream in(file);
   std::string line;
@@ -361,6 +362,11 @@ extern "C++" bool qcoll::tune_cache_find(const Plan &p, int64_t batch, const cha
     const long ck = (e1 != c0) ? std::strtol(e1, &e2, 10) : 0;
     const bool candidate = sch == 1 || (sch >= 0 && sch == onchip_candidate(p));   // -1: no on-chip one
     if (errno == 0 && e1 != c0 && e2 && e2 != e1 && candidate && ck >= 1 && ck <= 65536) {
+      // timed in a larger workspace: the next evaluation would not fit this one
+      Plan q = p;
+      q.schedule = int(sch);
+      q.chunk = int(ck);
+      if (make_layout(q, batch, 0, 0, ws_bytes).total > ws_bytes) continue;
       schedule = int(sch);
       chunk = int(ck);
       return true;
@@ -378,7 +384,7 @@ qcoll_status qcoll_autotune(qcoll_plan plan, int64_t batch, const double *f, dou
   const std::string key = tune_key(p, batch);
   const char *cache = std::getenv("QCOLL_AUTOTUNE_CACHE");
   int sch = 0, ck = 0;
-  if (cache && qcoll::tune_cache_find(p, batch, cache, sch, ck)) {
+  if (cache && qcoll::tune_cache_find(p, batch, ws_bytes, cache, sch, ck)) {
     p.schedule = sch;
     p.chunk = ck;
     ++p.gen;

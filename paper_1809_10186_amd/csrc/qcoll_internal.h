@@ -91,8 +91,8 @@ Layout make_layout(const Plan &p, int64_t batch, int op, long chunk = 0, size_t 
 // does not fit (lay.total says what it needs)
 constexpr size_t kScratchBytes = size_t(256) << 20;   // 256 MiB per device
 bool noalloc_layout(const Plan &p, int64_t batch, Layout &lay);
-// the first entry of an autotune cache file for this plan and batch
-bool tune_cache_find(const Plan &p, int64_t batch, const char *file, int &schedule, int &chunk);
+// the first entry of an autotune cache file for this plan and batch that fits the workspace
+bool tune_cache_find(const Plan &p, int64_t batch, size_t ws_bytes, const char *file, int &schedule, int &chunk);
 // the on-chip gain loop of nbp pairs is faster as one workgroup per term
 bool split_terms(const Plan &p, long nbp);
 

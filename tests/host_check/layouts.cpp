@@ -53,6 +53,8 @@ static void check_noalloc() {
           }
 }
 
+constexpr size_t kRoom = ~size_t(0);
+
 static void write_cache(const char *file, const char *text) {
   FILE *fp = std::fopen(file, "w");
   if (fp) {
@@ -68,19 +70,19 @@ static void check_tune_key(const char *file) {
   int sch = -7, ck = -7;
   write_cache(file, "gfx950 s2 N=24 Nr=8 M=12 prec=0 rank=8 batch<=64|1 32\n"
                     "gfx950 s3 N=24 Nr=8 M=12 prec=0 rank=8 batch<=64|1 32\n");
-  EXPECT(!qcoll::tune_cache_find(vhs, 50, file, sch, ck), "older set");
+  EXPECT(!qcoll::tune_cache_find(vhs, 50, kRoom, file, sch, ck), "older set");
   write_cache(file, "gfx950 s4 N=24 Nr=8 M=12 prec=0 rank=8 vss batch<=64|1 32\n"
                     "gfx950 s4 N=24 Nr=8 M=12 prec=0 rank=8 literal batch<=64|1 96\n");
-  EXPECT(!qcoll::tune_cache_find(vhs, 50, file, sch, ck), "VHS plan, VSS and literal entries");
-  EXPECT(qcoll::tune_cache_find(vss, 50, file, sch, ck) && sch == 1 && ck == 32, "%d %d", sch, ck);
-  EXPECT(qcoll::tune_cache_find(lit, 50, file, sch, ck) && sch == 1 && ck == 96, "%d %d", sch, ck);
-  EXPECT(!qcoll::tune_cache_find(vss, 65, file, sch, ck), "another batch");
+  EXPECT(!qcoll::tune_cache_find(vhs, 50, kRoom, file, sch, ck), "VHS plan, VSS and literal entries");
+  EXPECT(qcoll::tune_cache_find(vss, 50, kRoom, file, sch, ck) && sch == 1 && ck == 32, "%d %d", sch, ck);
+  EXPECT(qcoll::tune_cache_find(lit, 50, kRoom, file, sch, ck) && sch == 1 && ck == 96, "%d %d", sch, ck);
+  EXPECT(!qcoll::tune_cache_find(vss, 65, kRoom, file, sch, ck), "another batch");
   // small grids: larger candidates above 256 items, the older entries below
   const qcoll::Plan small = plan_of(8, 4, 6, QCOLL_FP32);
   write_cache(file, "gfx950 s2 N=8 Nr=4 M=6 prec=1 rank=4 batch<=256|2 192\n"
                     "gfx950 s2 N=8 Nr=4 M=6 prec=1 rank=4 batch<=512|2 256\n");
-  EXPECT(qcoll::tune_cache_find(small, 256, file, sch, ck) && sch == 2 && ck == 192, "%d %d", sch, ck);
-  EXPECT(!qcoll::tune_cache_find(small, 300, file, sch, ck), "256 items were the largest candidate");
+  EXPECT(qcoll::tune_cache_find(small, 256, kRoom, file, sch, ck) && sch == 2 && ck == 192, "%d %d", sch, ck);
+  EXPECT(!qcoll::tune_cache_find(small, 300, kRoom, file, sch, ck), "256 items were the largest candidate");
 }
 
 // schedules that are no candidate of the plan, negative ones among them
@@ -92,9 +94,23 @@ static void check_tune_schedule(const char *file) {
                     "gfx950 s4 N=24 Nr=8 M=12 prec=0 rank=8 batch<=64|2 64\n"
                     "gfx950 s4 N=24 Nr=8 M=12 prec=0 rank=8 batch<=64|0 40\n");
   int sch = -7, ck = -7;
-  EXPECT(!qcoll::tune_cache_find(plan_of(24, 8, 12, QCOLL_FP64, 1.5), 50, file, sch, ck), "%d %d", sch, ck);
-  EXPECT(qcoll::tune_cache_find(plan_of(24, 8, 12, QCOLL_FP64), 50, file, sch, ck) && sch == 0 && ck == 40, "%d %d", sch,
+  EXPECT(!qcoll::tune_cache_find(plan_of(24, 8, 12, QCOLL_FP64, 1.5), 50, kRoom, file, sch, ck), "%d %d", sch, ck);
+  EXPECT(qcoll::tune_cache_find(plan_of(24, 8, 12, QCOLL_FP64), 50, kRoom, file, sch, ck) && sch == 0 && ck == 40, "%d %d", sch,
          ck);
+}
+
+// a chunk timed in a larger workspace is no entry for one that does not hold it
+static void check_tune_fit(const char *file) {
+  qcoll::Plan p = plan_of(8, 4, 6, QCOLL_FP32);
+  write_cache(file, "gfx950 s4 N=8 Nr=4 M=6 prec=1 rank=4 batch<=2048|2 2048\n"
+                    "gfx950 s4 N=8 Nr=4 M=6 prec=1 rank=4 batch<=2048|2 256\n");
+  int sch = -7, ck = -7;
+  const size_t all = qcoll::make_layout(p, 2048, 0, 2048).total, part = qcoll::make_layout(p, 2048, 0, 256).total;
+  EXPECT(part < all, "%zu %zu", part, all);
+  EXPECT(qcoll::tune_cache_find(p, 2048, all, file, sch, ck) && ck == 2048, "%d", ck);
+  EXPECT(qcoll::tune_cache_find(p, 2048, all - 1, file, sch, ck) && ck == 256, "%d", ck);
+  EXPECT(qcoll::tune_cache_find(p, 2048, part, file, sch, ck) && ck == 256, "%d", ck);
+  EXPECT(!qcoll::tune_cache_find(p, 2048, part - 1, file, sch, ck), "%d", ck);
 }
 
 int main(int argc, char **argv) {
@@ -102,6 +118,7 @@ int main(int argc, char **argv) {
   if (!std::strcmp(what, "noalloc")) check_noalloc();
   else if (!std::strcmp(what, "tune_key") && argc > 2) check_tune_key(argv[2]);
   else if (!std::strcmp(what, "tune_schedule") && argc > 2) check_tune_schedule(argv[2]);
+  else if (!std::strcmp(what, "tune_fit") && argc > 2) check_tune_fit(argv[2]);
   else return 2;
   if (g_fail) {
     std::printf("layouts: %d failures\n", g_fail);

@@ -22,7 +22,7 @@ def driver(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("what", ["noalloc", "tune_key", "tune_schedule"])
+@pytest.mark.parametrize("what", ["noalloc", "tune_key", "tune_schedule", "tune_fit"])
 def test_layouts(driver, tmp_path, what):
     r = subprocess.run([driver, what, str(tmp_path / "cache.txt")], capture_output=True, text=True, timeout=300)
     print(r.stdout[-3000:], r.stderr[-1000:], flush=True)
