@@ -310,7 +310,7 @@ DgLayout dg_layout(qcoll_dg1d d, int rk) {
     l.off_ews = o;
     o += qcoll::al256(qcoll::make_layout(d->plan->p, l.items, 0).total);
   }
-  if (rk >= 1) {
+  if (rk == 1) {   // SSP-RK2 and RK3 form their stages in the transport's store
     l.off_r = o;
     o += qcoll::al256(vol);
   }
@@ -578,11 +578,11 @@ qcoll_status qcoll_dg1d_step(qcoll_dg1d d, double *F, double dt, int32_t rk, voi
   char *w = static_cast<char *>(ws);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const long n = long(d->I) * d->K * d->plan->p.n3();
-  double *Rb = reinterpret_cast<double *>(w + l.off_r);
   double *v1 = rk >= 2 ? reinterpret_cast<double *>(w + l.off_v1) : nullptr;
   double *v2 = rk >= 3 ? reinterpret_cast<double *>(w + l.off_v2) : nullptr;
   qcoll_status s;
   if (rk == 1) {   // in place: the update waits until every neighbour has read F
+    double *Rb = reinterpret_cast<double *>(w + l.off_r);
     if ((s = dg1d_rhs(d, F, Rb, w, l, st)) != QCOLL_OK) return s;
     return axpby3(F, F, 1.0, Rb, dt, nullptr, 0.0, n, st);
   }
