@@ -430,7 +430,9 @@ template <int N>
 static qcoll_status launch_fused_any(const Plan &p, const cplx<float> *H, cplx<float> *W, cplx<float> *U, long nbp,
                                      hipStream_t st) {
   if (p.is_vss()) return launch_fused<N, true>(p, H, W, U, nbp, st);
-  if (U) return launch_terms<N>(p, H, W, U, nbp, st);
+  if constexpr (N > 8) {   // split_terms never splits at 8^3
+    if (U) return launch_terms<N>(p, H, W, U, nbp, st);
+  }
   return launch_fused<N, false>(p, H, W, U, nbp, st);
 }
 
