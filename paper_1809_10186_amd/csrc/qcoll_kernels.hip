@@ -1238,6 +1238,15 @@ long eval_chunk(const Plan &p) {
   return p.N <= 8 ? 2048 : (p.N <= 12 ? 1024 : (p.N <= 16 ? 512 : (p.N <= 32 ? 256 : 64)));
 }
 
+// The same for the bilinear Q: at 16^3 in FP64 (two passes, whose volumes of a chunk
+// then leave the cache) about 768 pairs: M = 12, 256 items, N_rho 12, 64 / 128 / 256 a
+// chunk 1923 / 1959 / 2003 us, N_rho 5 945 / 852 / 883.
+static long bil_chunk(const Plan &p) {
+  if (p.N != 16 || p.precision != QCOLL_FP64) return eval_chunk(p);
+  const long n = 768 / p.N_rho;
+  return n < 64 ? 64 : (n > eval_chunk(p) ? eval_chunk(p) : n);
+}
+
 // The same for the vjp: the fused adjoint has no sub-chunks; the two-pass adjoint
 // keeps every term's volumes (FP64, M = 12, N_rho = 8, against 32 items: 1024 at
 // 8^3 3991 -> 892 us, 512 at 12^3 3291 -> 1458, 256 at 16^3 2347 -> 1502 and at 24^3
@@ -1312,7 +1321,7 @@ Layout make_layout(const Plan &p, int64_t batch, int op, long chunk, size_t ws_b
       return make_layout(p, batch, op, least_chunk(p, op), ws_bytes);
     return l;
   }
-  const long cmax = chunk > 0 ? chunk : (p.chunk > 0 ? p.chunk : eval_chunk(p));
+  const long cmax = chunk > 0 ? chunk : (p.chunk > 0 ? p.chunk : (op == 2 ? bil_chunk(p) : eval_chunk(p)));
   l.bc = batch < cmax ? (batch > 0 ? batch : 1) : cmax;
   const bool bil = (op == 2);
   // two-pass hot loop: (item, node) pairs per launch such that the launch's
