@@ -174,8 +174,13 @@ qcoll_status qcoll_plan_set_omega(qcoll_plan plan, double omega);
 qcoll_status qcoll_plan_set_schedule(qcoll_plan plan, int32_t schedule);
 
 /* Workspace needed by op 0 (qcoll_eval), 1 (qcoll_vjp) or 2 (qcoll_eval_bilinear)
- * for this batch.  A call given less runs in smaller chunks, down to 64 items
- * (op 1: 256 with the fused adjoint, 64 or 32 otherwise), with the same results. */
+ * for this batch in the plan's chunks.  With the default chunk (and for op 1, which
+ * has no other) a call given less runs in smaller chunks, with the same results, as
+ * long as the workspace holds 64 items (op 1: 256 with the fused adjoint, 64 for FP64
+ * VHS with N = 32 on chip, else 32): the size for that many items serves any batch and
+ * is the way to less memory, as is qcoll_plan_set_chunk (FP64, N = 32, N_rho = 16: about
+ * 2.6 GB for 256 items, 0.65 GB for 64).  After qcoll_plan_set_chunk or an autotune the
+ * chunk is fixed, and qcoll_eval, qcoll_eval_bilinear and what builds on them refuse less. */
 size_t qcoll_workspace_bytes(qcoll_plan plan, int64_t batch, int32_t op);
 
 /* Q(f,f) for every item (Appendix):
@@ -207,7 +212,8 @@ qcoll_status qcoll_eval_noalloc(qcoll_plan plan, int64_t batch, const double *f,
  * (t1_f t2_g + t2_f t1_g) / 2 (for VSS kernels each term's product is weighted
  * by its own alpha_pq after its transform), the loss is f * Lam~ g.  Q(f, f)
  * equals qcoll_eval.  Two inverse transforms per term (FP32 with N <= 32: on chip
- * for enough (item, node) pairs, with the same bits; otherwise two passes).  f, g, Q: [batch][N^3]; workspace: qcoll_workspace_bytes(op 2).
+ * for enough (item, node) pairs, with the same bits; otherwise two passes).
+ * f, g, Q: [batch][N^3]; workspace: qcoll_workspace_bytes(op 2).
  * ENOTSUP for literal-Nyquist plans. */
 qcoll_status qcoll_eval_bilinear(qcoll_plan plan, int64_t batch, const double *f, const double *g,
                                  double *Q, void *ws, size_t ws_bytes, void *stream);
@@ -291,20 +297,23 @@ qcoll_status qcoll_dg_collide_collocated(qcoll_plan plan, int64_t n_elem, int32_
                                          void *stream);
 
 /* Items per chunk of the eval pipeline (0 = default: 2048 at 8^3, 1024 at 12^3,
- * 512 at 16^3, 256 at 24^3 and 32^3, else 64; with a workspace too small for
- * that, 64); workspace sizes depend on it.  Results do not. */
+ * 512 at 16^3, 256 at 24^3 and 32^3, else 64, and 64 to 512 by N_rho for the FP64
+ * bilinear Q at 16^3; with a workspace too small for that, 64); workspace sizes
+ * depend on it.  Results do not. */
 qcoll_status qcoll_plan_set_chunk(qcoll_plan plan, int32_t items);
 
 /* Autotuner: times the candidate schedules of this plan (fused / two-pass hot
  * loop x 32, 64, 96, 128, 192, 256 items per chunk and a larger default chunk
  * where the workspace holds it, each balanced over the
- * batch as ceil(batch / ceil(batch / c)); best of two timed runs each) with qcoll_eval on the caller's f and Q (Q is overwritten), keeps the
- * fastest in the plan and returns it in
- * *host_schedule, *host_chunk (either may be NULL).  Synchronous.  If the
- * environment variable QCOLL_AUTOTUNE_CACHE names a file, choices are read
- * from and appended to it, keyed by (arch, the library's schedule set, N,
- * N_rho, M, precision, rank, batch rounded up to a power of two); entries of
- * an older schedule set are timed again. */
+ * batch as ceil(batch / ceil(batch / c)); best of two timed runs each) with
+ * qcoll_eval on the caller's f and Q (Q is overwritten), keeps the fastest in the
+ * plan and returns it in *host_schedule (1 two-pass, 2 on chip, or 0 on chip where
+ * that is the automatic choice but not one to request: FP64 VHS with N = 24),
+ * *host_chunk (either may be NULL).  Synchronous.  If the environment variable
+ * QCOLL_AUTOTUNE_CACHE names a file, choices are read from and appended to it, keyed
+ * by (arch, the library's schedule set, N, N_rho, M, precision, rank, VSS or literal
+ * plan, batch rounded up to a power of two); entries of an older schedule set, and
+ * those whose chunk does not fit the workspace, are timed again. */
 size_t qcoll_autotune_workspace_bytes(qcoll_plan plan, int64_t batch);
 qcoll_status qcoll_autotune(qcoll_plan plan, int64_t batch, const double *f, double *Q, void *ws,
                             size_t ws_bytes, void *stream, int32_t *host_schedule, int32_t *host_chunk);

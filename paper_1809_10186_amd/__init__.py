@@ -308,7 +308,7 @@ class Plan:
         return out
 
     def eval_bilinear(self, f, g, out=None, stream=None):
-        """Bilinear Q(f, g) for every item (two-pass schedule)."""
+        """Bilinear Q(f, g) for every item."""
         import torch
         batch = self._check_f(f, "f")
         if self._check_f(g, "g") != batch:
@@ -451,7 +451,8 @@ class Plan:
         self._ws = {}
 
     def autotune(self, f, Q=None, stream=None):
-        """Time the candidate schedules on f and keep the fastest; returns (schedule, chunk)."""
+        """Time the candidate schedules on f and keep the fastest; returns (schedule, chunk): 1 two-pass, 2 on chip, 0 on
+        chip where that is automatic only (see include/qcoll.h)."""
         import torch
         batch = self._check_f(f, "f")
         if Q is None:

@@ -387,7 +387,7 @@ static size_t adj_lds_bytes(int N, int M) {
 }
 
 // FP32 VHS plans with N <= 32 whose shift table fits next to the LDS work
-// area (160 KiB per CU; 32^3 holds M <= 112), unless the two-pass schedule was requested
+// area (160 KiB per CU; 32^3 holds M <= 96), unless the two-pass schedule was requested
 bool use_fused_adjoint(const Plan &p) {
   return p.schedule_user != 1 && !p.is_vss() && fused_gain_supported(p.N, p.precision) &&
          adj_lds_bytes(p.N, p.M) <= size_t(160) * 1024;

@@ -1,4 +1,5 @@
-// Body of the slab kernels over T, N, SIGN, src, dst, nslab and tile: text, not a
+// Body of the slab kernels over T, N, SIGN, the type Src of src, src, dst, nslab and
+// tile (a SlabTile<T, N> in LDS), which the including kernel declares: text, not a
 // function, because the compiler orders an inlined function's loads differently
 // (the shifted gain slab of 48^3 46.4 -> 47.0 us a launch).
   constexpr int SPB = slab_spb<T, N>();
