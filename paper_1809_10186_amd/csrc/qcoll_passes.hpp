@@ -93,14 +93,19 @@ struct grouped_loads<S, std::void_t<decltype(S::kGroupedLoads)>> : std::bool_con
 // computed once.  Lanes of a slab past the end read slab nslab - 1 (always
 // valid) and store nothing.  With SPLIT the real and imaginary parts take
 // turns in one tile.
-template <typename T, int N>
-struct SlabTile {
-  T v[slab_split<T, N>() ? 1 : 2][slab_spb<T, N>()][N][N + 1];
-};
+//
+// The LDS tiles of the real and the imaginary parts: two arrays, which the compiler
+// knows apart (as members of one struct the 32^3 FP32 pass of the VJP's h_p waited
+// for its loads one by one, 8 -> 16 us for one item); with SPLIT there is one.
+#define QC_SLAB_TILES                                                       \
+  constexpr int SPB = slab_spb<T, N>();                                     \
+  constexpr bool SPLIT = slab_split<T, N>();                                \
+  __shared__ T sre[SPB][N][N + 1];                                          \
+  __shared__ T sim[SPLIT ? 1 : SPB][SPLIT ? 1 : N][SPLIT ? 1 : N + 1]
 
 template <typename T, int N, int SIGN, class Src, class Dst>
 __global__ __launch_bounds__(256) void k_slab(Src src, Dst dst, long nslab) {
-  __shared__ SlabTile<T, N> tile;
+  QC_SLAB_TILES;
 #include "qcoll_slab_body.hpp"
 }
 
@@ -108,7 +113,7 @@ __global__ __launch_bounds__(256) void k_slab(Src src, Dst dst, long nslab) {
 // loss inverse of a small batch are launches of a few microseconds each
 template <typename T, int N, int SIGN, class S0, class D0, class S1, class D1>
 __global__ __launch_bounds__(256) void k_slab2(S0 s0, D0 d0, S1 s1, D1 d1, long nslab) {
-  __shared__ SlabTile<T, N> tile;
+  QC_SLAB_TILES;
   if (blockIdx.y == 0) {
     using Src = S0;
     const S0 &src = s0;

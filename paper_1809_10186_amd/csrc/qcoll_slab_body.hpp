@@ -1,9 +1,7 @@
 // Body of the slab kernels over T, N, SIGN, the type Src of src, src, dst, nslab and
-// tile (a SlabTile<T, N> in LDS), which the including kernel declares: text, not a
+// QC_SLAB_TILES, which the including kernel declares: text, not a
 // function, because the compiler orders an inlined function's loads differently
 // (the shifted gain slab of 48^3 46.4 -> 47.0 us a launch).
-  constexpr int SPB = slab_spb<T, N>();
-  constexpr bool SPLIT = slab_split<T, N>();
   const int s = int(threadIdx.x) / N, c = int(threadIdx.x) % N;
   const long g = long(blockIdx.x) * SPB + s;
   const long gl = g < nslab ? g : nslab - 1;
@@ -30,18 +28,17 @@
   fft_reg<N, SIGN, T>(xr, xi);
   if constexpr (SPLIT) {
     // one tile, one component at a time: column -> row, row FFT, row -> column
-    auto &sb = tile.v[0];
     const int row = c;
     auto to_rows = [&](T *x) {
-      static_for<0, N>([&](auto r) { sb[s][decltype(r)::value][c] = x[decltype(r)::value]; });
+      static_for<0, N>([&](auto r) { sre[s][decltype(r)::value][c] = x[decltype(r)::value]; });
       __syncthreads();
-      static_for<0, N>([&](auto k) { x[decltype(k)::value] = sb[s][row][decltype(k)::value]; });
+      static_for<0, N>([&](auto k) { x[decltype(k)::value] = sre[s][row][decltype(k)::value]; });
       __syncthreads();
     };
     auto to_cols = [&](T *x) {
-      static_for<0, N>([&](auto k) { sb[s][row][decltype(k)::value] = x[decltype(k)::value]; });
+      static_for<0, N>([&](auto k) { sre[s][row][decltype(k)::value] = x[decltype(k)::value]; });
       __syncthreads();
-      static_for<0, N>([&](auto r) { x[decltype(r)::value] = sb[s][decltype(r)::value][c]; });
+      static_for<0, N>([&](auto r) { x[decltype(r)::value] = sre[s][decltype(r)::value][c]; });
       __syncthreads();
     };
     to_rows(xr);
@@ -56,8 +53,6 @@
     }
     return;
   } else {
-    auto &sre = tile.v[0];
-    auto &sim = tile.v[1];
     static_for<0, N>([&](auto r) {
       sre[s][decltype(r)::value][c] = xr[decltype(r)::value];
       sim[s][decltype(r)::value][c] = xi[decltype(r)::value];
