@@ -1217,7 +1217,7 @@ bool split_terms(const Plan &p, long nbp) {
   const double u = 2.0 * p.n3() * (dp ? 16.0 : 8.0) / 7.0e6;
   const double n = double(nbp) * p.M;
   if (wgs * nbp > slots / 2) return false;
-  return std::ceil(wgs * n / slots) * t + n * u + 10.0 < t * p.M;
+  return std::ceil(wgs * n / slots) * t + n * u + 8.0 < t * p.M;
 }
 
 // items per launch of the FP64 on-chip term loops: two workgroups of every one of
